@@ -342,7 +342,7 @@ def run(st):
 
 def tolerance(c):
     if c["kind"] == "extract":
-            # a probability within rounding of its threshold flips its bit (measured: none did)
+        # a probability within rounding of its threshold flips its bit (measured: none did)
         return {"rel": 0.0, "differ": 1e-4}
     if c["dtype"] == "f32":
         return {"rel": 5e-6, "max": 5e-5}      # measured 0.8e-6 to 1.5e-6 off 64 bits
