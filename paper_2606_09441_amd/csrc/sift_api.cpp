@@ -39,6 +39,8 @@ struct sift_plan {
   int32_t* row_ptr = nullptr;  // [num_rows + 1]
   int32_t* col_idx = nullptr;  // [list_capacity]
   bool steps_paged = false;    // the last decode wrote page-pool rows into the steps
+  bool steps_decoded = false;  // the steps are the last decode's (not merged caller lists)
+  bool lists_own = false;      // the last decode wrote row_ptr and col_idx above
   hipStream_t last_stream = nullptr;  // the stream of the plan's last enqueued work
 };
 
@@ -791,6 +793,8 @@ sift_status sift_plan_decode_tiles(sift_plan* plan, const uint8_t* local_bitmap,
                                            static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return SIFT_E_HIP;
   plan->steps_paged = false;
+  plan->steps_decoded = true;
+  plan->lists_own = row_ptr == plan->row_ptr;
   plan->last_stream = static_cast<hipStream_t>(stream);
   return SIFT_OK;
 }
@@ -836,10 +840,12 @@ sift_status sift_sparse_attention(sift_plan* plan, const sift_tensor* q, const s
   if (bf16) {
     // the bf16 kernel walks merged per-unit step lists: build them from the lists
     e = sift::launch_merge_steps(plan->pt, work(plan), row_ptr, col_idx, col_capacity, s);
+    plan->steps_decoded = false;
     if (e == hipSuccess) plan->steps_paged = false;
     if (e == hipSuccess) e = sift::launch_attn_bf16(plan->pt, work(plan), a, s);
   } else {
-    e = sift::launch_attn_f32(plan->pt, a, s);
+    // the plan's steps stay the last decode's
+    e = sift::launch_attn_f32(plan->pt, nullptr, a, s);
   }
   plan->last_stream = s;
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
@@ -872,8 +878,13 @@ sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sif
   a.scale_log2 = softmax_scale * 1.4426950408889634f;
   a.out_f32 = out->dtype == SIFT_F32 ? 1 : 0;
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  const hipError_t e = q->dtype == SIFT_BF16 ? sift::launch_attn_bf16(plan->pt, work(plan), a, s)
-                                             : sift::launch_attn_f32(plan->pt, a, s);
+  // fp32 inputs: over the steps where they are the last decode's, for packed K and V
+  // (its only form when it wrote its lists to the caller's buffers)
+  const bool steps = plan->steps_decoded && !plan->steps_paged;
+  if (steps && !plan->lists_own) a.row_ptr = nullptr;
+  const hipError_t e = q->dtype == SIFT_BF16
+                           ? sift::launch_attn_bf16(plan->pt, work(plan), a, s)
+                           : sift::launch_attn_f32(plan->pt, steps ? &plan->wt : nullptr, a, s);
   plan->last_stream = s;
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }
@@ -929,6 +940,8 @@ sift_status sift_plan_run_paged(sift_plan* plan, const sift_tensor* q, const sif
   plan->last_stream = s;
   if (e != hipSuccess) return SIFT_E_HIP;
   plan->steps_paged = true;
+  plan->steps_decoded = true;
+  plan->lists_own = true;
   sift::AttnArgs a{};
   a.q = q->data;
   a.k = k_pages->data;
@@ -945,7 +958,7 @@ sift_status sift_plan_run_paged(sift_plan* plan, const sift_tensor* q, const sif
   a.out_f32 = out->dtype == SIFT_F32 ? 1 : 0;
   a.pages = pages;
   e = q->dtype == SIFT_BF16 ? sift::launch_attn_bf16(plan->pt, work(plan), a, s)
-                            : sift::launch_attn_f32(plan->pt, a, s);
+                            : sift::launch_attn_f32(plan->pt, &plan->wt, a, s);
   plan->last_stream = s;
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }

@@ -293,7 +293,11 @@ struct AttnArgs {
 // bf16 attention reads the merged step lists of wt (not row_ptr/col_idx).
 hipError_t launch_attn_bf16(const PlanTables& pt, const WorkTables& wt, const AttnArgs& a,
                             hipStream_t stream);
-hipError_t launch_attn_f32(const PlanTables& pt, const AttnArgs& a, hipStream_t stream);
+// fp32 attention reads row_ptr/col_idx or, where wt is not nullptr, may read
+// its merged steps and work records instead: those of the same lists (and
+// does where row_ptr is nullptr).
+hipError_t launch_attn_f32(const PlanTables& pt, const WorkTables* wt, const AttnArgs& a,
+                           hipStream_t stream);
 
 // Offline extraction (extract.hip).  One record per document; the bit-vector
 // offsets are those of the online path's buffers (document-major, query heads

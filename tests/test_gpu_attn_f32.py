@@ -1,0 +1,96 @@
+"""fp32 attention: the work-unit kernel (large calls) and the list kernel
+(small calls, caller-given lists) at the edges of their 16-row, 64-row and
+64-key blocks, against the fp64 oracle; packed, paged and over lists; and
+which lists an attention call on a plan uses after each kind of decode.
+
+The tolerance is the project's fp32 bar: scores of |s| <= 8 carry an error of
+about 128 * 2^-24 * |s| and as much again in the weights, 1e-6 in all for
+values of order one."""
+
+import numpy as np
+import pytest
+
+import gpu_helpers as G
+import workloads as W
+from oracle import sift_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+# (prompts, hq, hkv): groups of 64 rows over all heads below and above 512
+SMALL = ([[130, 17, 1, 40], [64, 16, 33]], 4, 2)
+UNITS = ([[200, 65, 1, 129, 30], [16, 48, 300, 64, 0]], 40, 5)
+SPLIT = ([[300] * 7 + [90]], 24, 8)     # a query long enough for pieces: 35 steps
+
+
+def _ref(wl):
+    return O.attention(G.oracle_layout(wl), wl.q, wl.k, wl.v, wl.la, wl.ca)
+
+
+@pytest.mark.parametrize("tile", [16, 32, 64])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("shape", [SMALL, UNITS, SPLIT], ids=["small", "units", "split"])
+def test_against_oracle(shape, d, tile):
+    import torch
+    prompts, hq, hkv = shape
+    wl = W.custom(prompts, tile=tile, hq=hq, hkv=hkv, d=d, dtype="f32", seed=tile + d)
+    dw = G.DevWorkload(wl)
+    ref = _ref(wl)
+    out = dw.run()
+    err = G.max_abs(out.cpu().numpy(), ref)
+    kp, vp, table = G.page_pool(wl, dw.k, dw.v)
+    paged = dw.plan.run_paged(dw.q, kp, vp, table, dw.la, dw.ca)
+    # packed K and V again over that decode, then over lists in the caller's buffers
+    after = dw.plan.attention_internal(dw.q, dw.k, dw.v)
+    rp, ci = dw.plan.decode(dw.la, dw.ca)
+    own = dw.plan.attention_internal(dw.q, dw.k, dw.v)
+    lists = dw.plan.attention(dw.q, dw.k, dw.v, rp, ci)
+    torch.cuda.synchronize()
+    errs = [G.max_abs(x.cpu().numpy(), ref) for x in (after, own, lists)]
+    G.say(f"f32 T={tile} D={d} {len(prompts)} prompts: max-abs {err:.2e}, after paged / own / lists "
+          + " ".join(f"{e:.2e}" for e in errs))
+    assert err <= G.F32_TOL and max(errs) <= G.F32_TOL
+    assert torch.equal(paged, out)
+    dw.close()
+
+
+def test_caller_lists_leave_the_decode_in_place():
+    """Attention over caller lists, then over the plan's decode: each its own."""
+    import torch
+    prompts, hq, hkv = UNITS
+    wl = W.custom(prompts, tile=32, hq=hq, hkv=hkv, d=64, dtype="f32", seed=3)
+    dw = G.DevWorkload(wl)
+    out = dw.run()
+    # lists of the diagonal tiles alone
+    M, rows = dw.plan.info["num_tiles"], dw.plan.info["num_rows"]
+    rp = torch.arange(rows + 1, dtype=torch.int32, device="cuda")
+    ci = torch.arange(M, dtype=torch.int32, device="cuda").repeat(hq)
+    diag = dw.plan.attention(dw.q, dw.k, dw.v, rp, ci)
+    again = dw.plan.attention_internal(dw.q, dw.k, dw.v)
+    torch.cuda.synchronize()
+    assert torch.equal(again, out) and not torch.equal(diag, out)
+    dw.close()
+
+
+def test_nan_reaches_only_rows_that_list_its_tile():
+    """A NaN key row: rows whose lists hold its tile become NaN, the others
+    stay as they were, in either kernel."""
+    import torch
+    for prompts, hq, hkv in (SMALL, UNITS):
+        wl = W.custom(prompts, tile=16, hq=hq, hkv=hkv, d=64, dtype="f32", seed=9)
+        dw = G.DevWorkload(wl)
+        rp, ci = dw.lists()
+        out = dw.run().cpu().numpy()
+        lay = G.oracle_layout(wl)
+        n = 2
+        _, _, a, cnt = lay.tile_span(n)
+        dw.k[a + cnt - 1] = float("nan")       # the tile's last key
+        got = dw.run().cpu().numpy()
+        for h in range(hq):
+            for m in range(lay.num_tiles):
+                _, _, b, c = lay.tile_span(m)
+                row = ci[rp[h * lay.num_tiles + m]: rp[h * lay.num_tiles + m + 1]]
+                if n not in row:
+                    assert np.array_equal(got[b:b + c, h], out[b:b + c, h]), (h, m)
+                elif m > n:
+                    assert np.isnan(got[b:b + c, h]).all(), (h, m)
+        dw.close()
