@@ -364,9 +364,14 @@ struct Emitter {
     }
   }
 
-  // The same with the tile's first K/V row and length already loaded.
+  // One round of a list walk: the M-blocks' lists, then the steps.
   __device__ __forceinline__ void emit_at(unsigned listed, int32_t n, int32_t row0, int32_t len) {
     lists(listed, n);
+    steps_at(listed, n, row0, len);
+  }
+
+  // T >= 64: the steps of tiles whose first K/V row and length are loaded.
+  __device__ __forceinline__ void steps_at(unsigned listed, int32_t n, int32_t row0, int32_t len) {
     if constexpr (!kHalves) {
       // T = 64: one step per listed tile, in lane order
       const unsigned long long mu = __ballot(listed != 0u);
@@ -486,6 +491,11 @@ struct Emitter {
   __device__ __forceinline__ void emit_grouped(unsigned listed, int32_t n, int32_t local, int32_t P,
                                                int lane) {
     lists(listed, n);
+    steps_grouped(listed, n, local, P, lane);
+  }
+
+  __device__ __forceinline__ void steps_grouped(unsigned listed, int32_t n, int32_t local,
+                                                int32_t P, int lane) {
     const int G = pt->group;
     unsigned gl[4];
     gl[0] = listed;
@@ -532,6 +542,17 @@ struct Emitter {
       wt->kvb[idx] = kb;
     }
     ps += __popcll(mu);
+  }
+
+  // The first steps of every piece of a split unit, read back from its
+  // finished list (the workgroup-scope fence waits for this wavefront's
+  // stores, which its CU's loads then see).
+  __device__ __forceinline__ void first_steps(int lane) {
+    __threadfence_block();
+    for (int q = lane; q < nw * kFirstSteps; q += 64) {
+      const int32_t k = q / kFirstSteps, j = q - k * kFirstSteps;
+      if (k * plen + j < ps - base) wt->rec[w0 + k].first[j] = steps[base + k * plen + j];
+    }
   }
 };
 
@@ -759,34 +780,20 @@ __global__ __launch_bounds__(256) void decode_write(PlanTables pt, WorkTables wt
     }
   }
   const int32_t cnt = e.ps - e.base;
-  if (!kGrouped && !e.whole) {
-    // the first steps of every piece, read back from the finished list (the
-    // workgroup-scope fence waits for this wavefront's stores, which its
-    // CU's loads then see)
-    __threadfence_block();
-    for (int q = lane; q < nw * kFirstSteps; q += 64) {
-      const int32_t k = q / kFirstSteps, j = q - k * kFirstSteps;
-      if (k * plen + j < cnt) wt.rec[e.w0 + k].first[j] = wt.steps[e.base + k * plen + j];
-    }
-  }
+  if (!kGrouped && !e.whole) e.first_steps(lane);
   if (ur.flags & kUnitLastPart) write_work_counts(wt, e.w0, nw, plen, cnt, lane, 64);
 }
 
-// Generic merge of caller-given lists (one thread per unit): the union of
-// the unit's rows, ascending, entries outside [first tile of the prompt,
-// M-block] skipped, at most lu_off[u+1] - lu_off[u] steps.
-__global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
-                                                   const int32_t* __restrict__ row_ptr,
-                                                   const int32_t* __restrict__ col,
-                                                   int64_t cap) {
-  const int u = blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= wt.num_units) return;
-  const int h = wt.lu_head[u];
-  const int m0 = wt.lu_m0[u];
-  const int nb = wt.lu_nb[u];
-  const int lo = pt.tile_lo[m0];
+// Merge of caller-given lists, one thread: the union of the unit's rows,
+// ascending, entries outside [first tile of the prompt, M-block] skipped, at
+// most as many steps as the unit's walk has.  Returns their number.  Only for
+// lists that do not ascend strictly (merge_steps).
+__device__ int merge_serial(const PlanTables& pt, const WorkTables& wt,
+                                         const UnitRec& ur, const int32_t* __restrict__ row_ptr,
+                                         const int32_t* __restrict__ col, int64_t cap) {
+  const int m0 = ur.m0, nb = ur.nb, lo = ur.lo;
   const int G = pt.group;
-  const int64_t r0 = static_cast<int64_t>(h) * pt.num_tiles + m0;
+  const int64_t r0 = static_cast<int64_t>(ur.head) * pt.num_tiles + m0;
   auto clampi = [cap](int64_t x) { return min(cap, max(static_cast<int64_t>(0), x)); };
   int64_t it[kMaxListBlocks], end[kMaxListBlocks];
 #pragma unroll
@@ -798,12 +805,12 @@ __global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
       end[k] = max(it[k], clampi(row_ptr[r0 + k + 1]));
     }
   }
-  const int base = wt.lu_off[u];
-  const int room = wt.lu_off[u + 1] - base;
+  const int base = ur.step_off;
+  const int room = (m0 + nb - lo) * pt.halves;
   int ns = 0;
-  int pw = wt.lu_work0[u];        // work unit of the next step
-  int pj = 0;                     // its place in that piece
-  const int plen = wt.lu_len[u];  // piece length
+  int pw = ur.work0;          // work unit of the next step
+  int pj = 0;                 // its place in that piece
+  const int plen = ur.plen;   // piece length
   auto put = [&](int2 st, uint32_t sm) {
     if (G > 1) {
       wt.kvb[base + ns] = make_int4(st.x, st.x, st.x, st.x);  // adjacent tiles
@@ -884,7 +891,120 @@ __global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
     }
   }
   if (G > 1 && ns < room) flush();
-  write_work_counts(wt, wt.lu_work0[u], wt.lu_nwork[u], plen, ns, 0, 1);
+  return ns;
+}
+
+// Merged steps of caller-given lists: one wavefront per list unit walks the
+// prompt's tiles 64 at a time, as the decode does, and takes each M-block's
+// entries of the window from its list (64 loaded per M-block, those of the
+// window being consecutive and distinct where the list ascends strictly),
+// through a byte per tile in LDS to the tile's lane.  A list that does not
+// ascend strictly is merged by one lane instead.
+// Bound by latency: one dependent load per window.  One thread per unit took
+// 301 us for 260 tiles x 32 heads (T = 64); this takes 18.
+template <int kNb, bool kGrouped, bool kHalves>
+__global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
+                                                   const int32_t* __restrict__ row_ptr,
+                                                   const int32_t* __restrict__ col, int64_t cap) {
+  __shared__ uint8_t marks[4][kNb][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int slot = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave);
+  if (slot >= wt.num_urec) return;  // uniform per wavefront, no barrier below
+  const UnitRec ur = wt.urec[slot];
+  if (!(ur.flags & kUnitFirstPart)) return;  // the unit's other parts
+  const int m0 = ur.m0, nb = ur.nb, lo = ur.lo, mlast = m0 + nb - 1;
+  const int64_t r0 = static_cast<int64_t>(ur.head) * pt.num_tiles + m0;
+  // row_ptr holds 32-bit offsets, so clamped ones fit 32 bits too
+  auto clampi = [cap](int32_t x) {
+    return static_cast<int32_t>(min(cap, static_cast<int64_t>(max(0, x))));
+  };
+  int32_t it[kNb], end[kNb];
+#pragma unroll
+  for (int k = 0; k < kNb; ++k) {
+    it[k] = k < nb ? clampi(row_ptr[r0 + k]) : 0;
+    end[k] = k < nb ? max(it[k], clampi(row_ptr[r0 + k + 1])) : 0;
+  }
+  Emitter<kNb, kHalves> e;
+  e.steps = wt.steps;
+  e.pt = &pt;
+  e.wt = &wt;
+  e.pages = KvPages{nullptr, 0};
+  e.base = e.ps = ur.step_off;
+  e.w0 = ur.work0;
+  e.nw = ur.nwork;
+  e.whole = e.nw == 1;
+  e.plen = ur.plen;
+  e.m0 = m0;
+  e.nb = nb;
+  e.hrows = static_cast<unsigned>((ur.flags >> 1) & 3);
+  e.below = (1ull << lane) - 1ull;
+  bool sorted = true;  // uniform
+  // bit k: M-block m0 + k lists tile n0 + lane; entries below n1 are consumed
+  auto window = [&](int n0, int n1) {
+    unsigned listed = 0u;
+#pragma unroll
+    for (int k = 0; k < kNb; ++k) {
+      if (k >= nb) break;
+      // volatile: a lane reads what other lanes wrote
+      volatile uint8_t* mk = marks[wave][k];
+      mk[lane] = 0;
+      int32_t before = INT32_MIN;  // the last entry of the load before
+      for (;;) {
+        const int32_t idx = it[k] + lane;
+        const int32_t n = idx < end[k] && idx >= it[k] ? col[idx] : INT32_MAX;
+        int32_t prev = __shfl_up(n, 1, 64);
+        if (lane == 0) prev = before;
+        const unsigned long long in = __ballot(n < n1);
+        // the entries below n1 lead, ascend and, past the first window, start at n0
+        sorted = sorted && (in & (in + 1ull)) == 0ull &&
+                 __ballot(n < n1 && (n <= prev || (n < n0 && n0 != lo))) == 0ull;
+        if (n >= n0 && n < n1 && n <= m0 + k) mk[n - n0] = 1;
+        const int adv = __popcll(in);
+        it[k] += adv;
+        if (adv < 64 || !sorted) break;
+        before = __builtin_amdgcn_readlane(n, 63);
+      }
+      listed |= static_cast<unsigned>(mk[lane]) << k;
+    }
+    return listed;
+  };
+  if constexpr (!kGrouped) {
+    const int2* rowlen = reinterpret_cast<const int2*>(pt.tile_info);  // {first row, length} at 2 n
+    for (int n0 = lo; n0 <= mlast && sorted; n0 += 64) {
+      const int n = n0 + lane;
+      const int2 rl = rowlen[2 * min(n, mlast)];
+      const unsigned listed = window(n0, min(n0 + 64, mlast + 1));
+      e.steps_at(listed, n, rl.x, rl.y);
+    }
+  } else {
+    // segment by segment: a step's group of tiles stays within one window
+    for (int d = ur.part_d0; d <= ur.seg && sorted; ++d) {
+      const int t0 = pt.seg_tile0[d], P = pt.seg_pages[d];
+      const int last = d < ur.seg ? P - 1 : mlast - t0;
+      for (int c0 = 0; c0 <= last && sorted; c0 += 64) {
+        const unsigned listed = window(t0 + c0, min(t0 + c0 + 64, t0 + last + 1));
+        e.steps_grouped(listed, t0 + c0 + lane, c0 + lane, P, lane);
+      }
+    }
+  }
+  // nothing but entries to skip may be left
+#pragma unroll
+  for (int k = 0; k < kNb; ++k) {
+    for (int32_t i0 = it[k]; k < nb && i0 < end[k] && sorted; i0 += min(64, end[k] - i0)) {
+      const int32_t n = lane < end[k] - i0 ? col[i0 + lane] : INT32_MAX;
+      sorted = __ballot(n >= lo && n <= m0 + k) == 0ull;
+    }
+  }
+  int cnt = e.ps - e.base;
+  if (sorted) {
+    if (!kGrouped && !e.whole) e.first_steps(lane);
+  } else {
+    __threadfence_block();  // the steps written so far are written before they are replaced
+    if (lane == 0) cnt = merge_serial(pt, wt, ur, row_ptr, col, cap);
+    cnt = __builtin_amdgcn_readfirstlane(cnt);
+  }
+  write_work_counts(wt, e.w0, e.nw, e.plen, cnt, lane, 64);
 }
 
 // Schedule pass, blocks x sched_blocks .. for chunk x: each scans the
@@ -995,8 +1115,19 @@ hipError_t launch_decode(const PlanTables& pt, const WorkTables& wt, const uint8
 hipError_t launch_merge_steps(const PlanTables& pt, const WorkTables& wt, const int32_t* row_ptr,
                               const int32_t* col_idx, int64_t col_capacity, hipStream_t stream) {
   if (wt.num_units == 0) return hipSuccess;
-  hipLaunchKernelGGL(merge_steps, dim3(static_cast<unsigned>((wt.num_units + 255) / 256)),
-                     dim3(256), 0, stream, pt, wt, row_ptr, col_idx, col_capacity);
+  const dim3 grid(static_cast<unsigned>((wt.num_urec + 3) / 4));
+  if (pt.group == 4)
+    hipLaunchKernelGGL((merge_steps<8, true, false>), grid, dim3(256), 0, stream, pt, wt, row_ptr,
+                       col_idx, col_capacity);
+  else if (pt.group == 2)
+    hipLaunchKernelGGL((merge_steps<4, true, false>), grid, dim3(256), 0, stream, pt, wt, row_ptr,
+                       col_idx, col_capacity);
+  else if (pt.halves == 2)
+    hipLaunchKernelGGL((merge_steps<2, false, true>), grid, dim3(256), 0, stream, pt, wt, row_ptr,
+                       col_idx, col_capacity);
+  else
+    hipLaunchKernelGGL((merge_steps<2, false, false>), grid, dim3(256), 0, stream, pt, wt, row_ptr,
+                       col_idx, col_capacity);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_schedule(wt, stream);

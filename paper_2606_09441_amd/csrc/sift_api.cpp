@@ -510,13 +510,6 @@ sift_status create_plan(const sift_layout* layout, int32_t num_q_heads, int32_t 
   const size_t o_tile_len = put(blob, hp.tile_len);
   const size_t o_tile_lo = put(blob, hp.tile_lo);
   const size_t o_tile_info = put(blob, hp.tile_info);
-  const size_t o_uh = put(blob, hp.unit_head);
-  const size_t o_um0 = put(blob, hp.unit_m0);
-  const size_t o_unb = put(blob, hp.unit_nb);
-  const size_t o_soff = put(blob, hp.step_off);
-  const size_t o_lw0 = put(blob, hp.lu_work0);
-  const size_t o_lnw = put(blob, hp.lu_nwork);
-  const size_t o_llen = put(blob, hp.lu_len);
   const size_t o_urec = put(blob, hp.urec);
   const size_t o_rec = put(blob, hp.rec);  // step counts and first steps: written by decode
   const size_t o_launch = put(blob, hp.launch);  // written by the schedule pass
@@ -624,13 +617,6 @@ sift_status create_plan(const sift_layout* layout, int32_t num_q_heads, int32_t 
   plan->wt.rec = reinterpret_cast<sift::WorkRec*>(P(o_rec));
   plan->wt.launch = reinterpret_cast<sift::WorkRec*>(P(o_launch));
   plan->wt.hist = P(o_hist);
-  plan->wt.lu_head = P(o_uh);
-  plan->wt.lu_m0 = P(o_um0);
-  plan->wt.lu_nb = P(o_unb);
-  plan->wt.lu_off = P(o_soff);
-  plan->wt.lu_work0 = P(o_lw0);
-  plan->wt.lu_nwork = P(o_lnw);
-  plan->wt.lu_len = P(o_llen);
   plan->wt.urec = reinterpret_cast<const sift::UnitRec*>(P(o_urec));
   plan->wt.steps = reinterpret_cast<int2*>(P(o_steps));
   plan->wt.kvb = tile < 64 ? reinterpret_cast<int4*>(P(o_kvb)) : nullptr;

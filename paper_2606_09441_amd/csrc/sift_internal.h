@@ -53,8 +53,8 @@ __device__ __forceinline__ int32_t kv_row0(const PlanTables& pt, const KvPages& 
 
 // Attention work: a list unit = (query head, up to kUnitBlocks consecutive
 // M-blocks of one segment).  The decode pass writes each list unit's merged
-// step list (the union of its M-blocks' lists) at steps[lu_off[u] ..];
-// lu_off[u+1] - lu_off[u] bounds its length.
+// step list (the union of its M-blocks' lists) at steps[step_off ..] of its
+// record, which has room for every tile up to its last M-block.
 // Step = {first K/V row of the key tile, len | listed << 8 | diagonal << 12},
 // where bit k of `listed` says M-block m0 + k lists the tile and bit k of
 // `diagonal` says the tile is m0 + k itself.  At T < 64 a step is 64 keys of
@@ -70,8 +70,8 @@ __device__ __forceinline__ int32_t kv_row0(const PlanTables& pt, const KvPages& 
 // (O normalised by its own row sum, in the output's type; reference max; row
 // sum) to a slot of the partial scratch, and a combine pass merges the pieces
 // of every split unit into the output.
-// List unit u owns work units lu_work0[u] .. + lu_nwork[u] - 1, piece k
-// covering its steps [k * lu_len[u], (k + 1) * lu_len[u]).
+// A list unit owns work units work0 .. + nwork - 1 of its record, piece k
+// covering its steps [k * plen, (k + 1) * plen).
 //
 // Every work unit has a 64-byte record that holds all a workgroup needs
 // before its first K/V fetch, so the kernel's start is one scalar load deep.
@@ -134,7 +134,7 @@ struct alignas(64) UnitRec {
   int32_t sd0;                // first tile of the segment
   int32_t pages;              // the segment's pages
   int32_t la_off;             // its LA vectors' byte offset (head 0)
-  int32_t step_off;           // first step of the unit's merged list (lu_off)
+  int32_t step_off;           // first step of the unit's merged list
   int32_t work0, nwork, plen;  // its work units: nwork pieces of plen steps from work0
   int32_t flags;              // kUnitQuery | hrows << 1 (T = 128: kernel blocks of the
                               // M-block, 3 or 1) | kUnitFirstPart | kUnitLastPart
@@ -151,17 +151,9 @@ struct WorkTables {
   WorkRec* launch;            // [grid] launch order (device scratch, written by the schedule pass)
   int32_t* hist;              // [kNumXcd * kSchedBuckets] bucket sizes (device scratch, zero
                               // between decodes)
-  // list units (decode)
-  const int32_t* lu_head;     // [U]
-  const int32_t* lu_m0;       // [U]
-  const int32_t* lu_nb;       // [U]
-  const int32_t* lu_off;      // [U + 1]
-  const int32_t* lu_work0;    // [U]
-  const int32_t* lu_nwork;    // [U]
-  const int32_t* lu_len;      // [U] piece length (a bound of the list when not split)
-  const UnitRec* urec;        // [U] the list units in decode write order
-  int2* steps;                // [lu_off[U]] (device scratch)
-  int4* kvb;                  // [lu_off[U]] per step, T < 64 only: word q = the first K/V row
+  const UnitRec* urec;        // [num_urec] the list units, or their parts, in decode write order
+  int2* steps;                // the list units' steps, one unit after another (device scratch)
+  int4* kvb;                  // per step, T < 64 only: word q = the first K/V row
                               // of the step's key sub-tile q minus q T (the step's 64 keys
                               // are G tiles, not always adjacent ones; words past the
                               // step's tiles repeat a valid one) (device scratch)
