@@ -22,6 +22,7 @@ struct ExtractPlan {
   size_t la_bytes = 0, ca_bytes = 0;
   size_t o_docs = 0, o_blocks = 0, o_flags = 0, o_counts = 0, end = 0;
   int64_t flag_bytes = 0, count_words = 0;
+  int32_t max_len = 0;  // tokens of the longest document
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -42,6 +43,7 @@ sift_status build_extract_plan(int32_t num_docs, const int32_t* offs, int32_t hq
     sift::ExtractDoc& e = ep.docs[d];
     e.tok0 = offs[d];
     e.len = static_cast<int32_t>(len);
+    ep.max_len = std::max(ep.max_len, e.len);
     e.P = static_cast<int32_t>(P);
     e.pad = 0;
     e.la_off = la;
@@ -144,7 +146,7 @@ sift_status sift_extract_bits(const sift_tensor* q, const sift_tensor* k, int32_
   a.gamma = gamma;
   const int64_t zero_words = static_cast<int64_t>((ep.end - ep.o_flags) / 4);
   const hipError_t e = sift::launch_extract(
-      a, num_docs, static_cast<int32_t>(ep.blocks.size() / 2), q->head_dim, tile,
+      a, num_docs, static_cast<int32_t>(ep.blocks.size() / 2), ep.max_len, q->head_dim, tile,
       reinterpret_cast<uint32_t*>(ws + ep.o_flags), zero_words, la_out, ca_out, s);
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }

@@ -319,9 +319,10 @@ struct ExtractArgs {
 };
 
 // Zeroes zero_words_n words at zero_base (the flags and counts), runs the
-// extraction over num_blocks query blocks x hq heads, then packs the bits.
+// extraction over num_blocks query blocks x hq heads (documents of at most
+// max_len tokens), then packs the bits.
 hipError_t launch_extract(const ExtractArgs& a, int32_t num_docs, int32_t num_blocks,
-                          int32_t head_dim, int32_t tile, uint32_t* zero_base, int64_t zero_words_n,
+                          int32_t max_len, int32_t head_dim, int32_t tile, uint32_t* zero_base, int64_t zero_words_n,
                           uint8_t* la, uint8_t* ca, hipStream_t stream);
 
 // Rotary position embedding of q [tokens][hq][D] and k [tokens][hkv][D]
