@@ -96,6 +96,8 @@ _SIGS = {
                                                   ctypes.POINTER(SiftTensor), _P]),
     "sift_static_scratch_bytes": (ctypes.c_size_t, []),
     "sift_rope": (ctypes.c_int, [ctypes.POINTER(SiftTensor), ctypes.POINTER(SiftTensor), _P, _P, _P]),
+    "sift_rms_norm": (ctypes.c_int, [_P, _P, ctypes.c_int64, ctypes.c_int32, ctypes.c_float, _P, _P]),
+    "sift_silu_mul": (ctypes.c_int, [_P, _P, ctypes.c_int64, _P, _P]),
     "sift_extract_sizes": (ctypes.c_int, [ctypes.c_int32, _P, ctypes.c_int32, ctypes.c_int32,
                                           ctypes.POINTER(ctypes.c_size_t), ctypes.POINTER(ctypes.c_size_t),
                                           ctypes.POINTER(ctypes.c_size_t)]),
@@ -528,6 +530,46 @@ def rope_(q, k, positions, inv_freq, stream=None):
     check("sift_rope", lib().sift_rope(ctypes.byref(qd), ctypes.byref(kd), _ptr(positions),
                                        _ptr(inv_freq), _stream_ptr(stream)))
     return q, k
+
+
+def _plain(*ts) -> bool:
+    """Whether the library can take these tensors as they are, in place of
+    framework operations on them: bf16, contiguous, 16-byte aligned, on one
+    GPU, and nothing recorded or transformed (autograd, forward mode,
+    tracing, tensor subclasses)."""
+    torch = _torch()
+    if torch.jit.is_tracing() or torch.autograd.forward_ad._current_level >= 0:
+        return False
+    grad = torch.is_grad_enabled()
+    return all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda
+               and t.device == ts[0].device and t.dtype == torch.bfloat16 and t.is_contiguous()
+               and not (grad and t.requires_grad) and t.data_ptr() % 16 == 0 for t in ts)
+
+
+def rms_norm(x, weight, eps: float, stream=None):
+    """RMSNorm of the rows of x [rows, width] (sift_rms_norm).  None when the
+    library does not take these tensors."""
+    torch = _torch()
+    if not (_plain(x, weight) and x.dim() == 2 and weight.shape == x.shape[1:]
+            and 8 <= x.shape[1] <= 16384 and x.shape[1] % 8 == 0 and x.shape[0] < 1 << 24
+            and x.device.index == torch.cuda.current_device()):
+        return None
+    out = torch.empty_like(x)
+    check("sift_rms_norm", lib().sift_rms_norm(_ptr(x), _ptr(weight), x.shape[0], x.shape[1],
+                                               ctypes.c_float(eps), _ptr(out), _stream_ptr(stream)))
+    return out
+
+
+def silu_mul(gate, up, stream=None):
+    """silu(gate) * up (sift_silu_mul), in gate's memory.  None when the
+    library does not take these tensors."""
+    torch = _torch()
+    if not (_plain(gate, up) and gate.shape == up.shape and gate.numel() % 8 == 0
+            and gate.device.index == torch.cuda.current_device()):
+        return None
+    check("sift_silu_mul", lib().sift_silu_mul(_ptr(gate), _ptr(up), gate.numel(), _ptr(gate),
+                                               _stream_ptr(stream)))
+    return gate
 
 
 def default_scale(head_dim: int) -> float:

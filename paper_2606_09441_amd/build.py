@@ -21,7 +21,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB_PATH = os.path.join(HERE, "libsift.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["decode.hip", "attn_bf16.hip", "attn_f32.hip", "extract.hip", "rope.hip", "sift_api.cpp",
+SOURCES = ["decode.hip", "attn_bf16.hip", "attn_f32.hip", "extract.hip", "rope.hip", "layer_ops.hip", "sift_api.cpp",
            "extract_api.cpp", "layer_api.cpp"]
 # Per-source extra flags.  The bf16 attention kernel takes row maxima of MFMA
 # results that are finite or -inf (masked): NaN canonicalisation around

@@ -1,6 +1,7 @@
 // C ABI of the pieces the decoder-layer prefill slice adds around the sparse
-// attention: the rotary position embedding (rope.hip).  The projections are
-// library GEMMs called by the caller.
+// attention: the rotary position embedding (rope.hip), the norms and the
+// SwiGLU product (layer_ops.hip).  The projections are library GEMMs called
+// by the caller.
 
 #include <hip/hip_runtime.h>
 
@@ -8,6 +9,10 @@
 
 #include "sift.h"
 #include "sift_internal.h"
+
+namespace {
+bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+}  // namespace
 
 extern "C" {
 
@@ -25,6 +30,31 @@ sift_status sift_rope(const sift_tensor* q, const sift_tensor* k, const int32_t*
   const hipError_t e = sift::launch_rope(q->data, q->tokens, q->heads, k->data, k->heads,
                                          q->head_dim, positions, inv_freq,
                                          static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
+}
+
+sift_status sift_rms_norm(const void* x, const void* weight, int64_t rows, int32_t width, float eps,
+                          void* out, void* stream) {
+  if (rows < 0 || width < 1) return SIFT_E_SHAPE;
+  if (rows == 0) return SIFT_OK;
+  if (x == nullptr || weight == nullptr || out == nullptr) return SIFT_E_NULL;
+  if (width % 8 != 0 || width > sift::kMaxNormWidth) return SIFT_E_UNSUPPORTED;
+  if (!aligned16(x) || !aligned16(weight) || !aligned16(out)) return SIFT_E_UNSUPPORTED;
+  if (rows >= int64_t(1) << 24) return SIFT_E_CAPACITY;  // a grid holds fewer than 2^32 threads
+  const hipError_t e = sift::launch_rms_norm(x, weight, rows, width, eps, out,
+                                             static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
+}
+
+sift_status sift_silu_mul(const void* gate, const void* up, int64_t count, void* out,
+                          void* stream) {
+  if (count < 0) return SIFT_E_SHAPE;
+  if (count == 0) return SIFT_OK;
+  if (gate == nullptr || up == nullptr || out == nullptr) return SIFT_E_NULL;
+  if (count % 8 != 0 || !aligned16(gate) || !aligned16(up) || !aligned16(out))
+    return SIFT_E_UNSUPPORTED;
+  const hipError_t e =
+      sift::launch_silu_mul(gate, up, count, out, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }
 

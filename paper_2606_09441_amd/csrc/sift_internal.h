@@ -330,4 +330,13 @@ hipError_t launch_extract(const ExtractArgs& a, int32_t num_docs, int32_t num_bl
 hipError_t launch_rope(void* q, int64_t tokens, int hq, void* k, int hkv, int head_dim,
                        const int32_t* positions, const float* inv_freq, hipStream_t stream);
 
+// RMSNorm of rows x width bf16 values and silu(gate) * up of count bf16 values
+// (layer_ops.hip); 16-byte aligned, width a multiple of 8 up to
+// kMaxNormWidth, count a multiple of 8.
+constexpr int kMaxNormWidth = 16384;
+hipError_t launch_rms_norm(const void* x, const void* weight, int64_t rows, int width, float eps,
+                           void* out, hipStream_t stream);
+hipError_t launch_silu_mul(const void* gate, const void* up, int64_t count, void* out,
+                           hipStream_t stream);
+
 }  // namespace sift

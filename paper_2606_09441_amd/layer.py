@@ -4,15 +4,16 @@ One pre-norm layer of the Llama-3.1-8B architecture (the model of Section 6):
 RMSNorm, the q/k/v projections, rotary embedding (libsift's `sift_rope`), the
 sparse attention (libsift's plan: decode + attention over the bits), the
 output projection and residual, then optionally the SwiGLU MLP.  The
-projections are library GEMMs (torch.matmul -> hipBLASLt on bf16); the norm
-and the MLP activation are torch elementwise ops.  It serves to measure the
+projections are library GEMMs (torch.matmul -> hipBLASLt on bf16); the norms
+and the MLP activation are one kernel each, or torch elementwise ops for
+tensors that those do not take (other types or widths, recorded gradients).  It serves to measure the
 per-layer prefill time of sparse against dense attention, the quantity the
 paper's time-to-first-token results aggregate (Section 7).
 """
 
 from __future__ import annotations
 
-from ._lib import _torch, rope_
+from ._lib import _torch, rms_norm, rope_, silu_mul
 
 
 class PrefillLayer:
@@ -31,6 +32,9 @@ class PrefillLayer:
         self.Wq, self.Wk, self.Wv = W[:qd], W[qd:qd + kd], W[qd + kd:qd + 2 * kd]
 
     def _norm(self, x, w):
+        y = rms_norm(x, w, self.eps)
+        if y is not None:
+            return y
         torch = _torch()
         xf = x.float()
         y = xf * torch.rsqrt(xf.pow(2).mean(-1, keepdim=True) + self.eps) * w.float()
@@ -55,4 +59,7 @@ class PrefillLayer:
         h2 = self._norm(x1, self.w["w_post"])
         g = h2 @ self.w["Wg"].T
         u = h2 @ self.w["Wu"].T
-        return x1 + (torch.nn.functional.silu(g) * u) @ self.w["Wd"].T
+        act = silu_mul(g, u)
+        if act is None:
+            act = torch.nn.functional.silu(g) * u
+        return x1 + act @ self.w["Wd"].T
