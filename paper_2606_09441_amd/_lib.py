@@ -96,8 +96,6 @@ _SIGS = {
                                                   ctypes.POINTER(SiftTensor), _P]),
     "sift_static_scratch_bytes": (ctypes.c_size_t, []),
     "sift_rope": (ctypes.c_int, [ctypes.POINTER(SiftTensor), ctypes.POINTER(SiftTensor), _P, _P, _P]),
-    "sift_rms_norm": (ctypes.c_int, [_P, _P, ctypes.c_int64, ctypes.c_int32, ctypes.c_float, _P, _P]),
-    "sift_silu_mul": (ctypes.c_int, [_P, _P, ctypes.c_int64, _P, _P]),
     "sift_extract_sizes": (ctypes.c_int, [ctypes.c_int32, _P, ctypes.c_int32, ctypes.c_int32,
                                           ctypes.POINTER(ctypes.c_size_t), ctypes.POINTER(ctypes.c_size_t),
                                           ctypes.POINTER(ctypes.c_size_t)]),
@@ -105,6 +103,13 @@ _SIGS = {
                                          ctypes.c_int32, _P, ctypes.c_int32, ctypes.c_double,
                                          ctypes.c_double, ctypes.c_double, ctypes.c_float, _P, _P, _P,
                                          ctypes.c_size_t, _P]),
+}
+
+# entries of the decoder layer (csrc/layer_api.h), not part of sift.h
+_LAYER_SIGS = {
+    "sift_layer_rms_norm": (ctypes.c_int, [_P, _P, ctypes.c_int64, ctypes.c_int32, ctypes.c_float, _P,
+                                           _P]),
+    "sift_layer_silu_mul": (ctypes.c_int, [_P, _P, ctypes.c_int64, _P, _P]),
 }
 
 _lib = None
@@ -127,7 +132,7 @@ def lib() -> ctypes.CDLL:
             raise RuntimeError(f"{LIB_PATH} is missing: build it with "
                                "`python -m paper_2606_09441_amd.build` (no fallback exists)")
         L = ctypes.CDLL(LIB_PATH)
-        for name, (res, args) in _SIGS.items():
+        for name, (res, args) in (*_SIGS.items(), *_LAYER_SIGS.items()):
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
@@ -547,28 +552,29 @@ def _plain(*ts) -> bool:
 
 
 def rms_norm(x, weight, eps: float, stream=None):
-    """RMSNorm of the rows of x [rows, width] (sift_rms_norm).  None when the
-    library does not take these tensors."""
+    """RMSNorm of the rows of x [rows, width] (sift_layer_rms_norm).  None when
+    the library does not take these tensors."""
     torch = _torch()
     if not (_plain(x, weight) and x.dim() == 2 and weight.shape == x.shape[1:]
             and 8 <= x.shape[1] <= 16384 and x.shape[1] % 8 == 0 and x.shape[0] < 1 << 24
             and x.device.index == torch.cuda.current_device()):
         return None
     out = torch.empty_like(x)
-    check("sift_rms_norm", lib().sift_rms_norm(_ptr(x), _ptr(weight), x.shape[0], x.shape[1],
-                                               ctypes.c_float(eps), _ptr(out), _stream_ptr(stream)))
+    check("sift_layer_rms_norm", lib().sift_layer_rms_norm(
+        _ptr(x), _ptr(weight), x.shape[0], x.shape[1], ctypes.c_float(eps), _ptr(out),
+        _stream_ptr(stream)))
     return out
 
 
 def silu_mul(gate, up, stream=None):
-    """silu(gate) * up (sift_silu_mul), in gate's memory.  None when the
+    """silu(gate) * up (sift_layer_silu_mul), in gate's memory.  None when the
     library does not take these tensors."""
     torch = _torch()
     if not (_plain(gate, up) and gate.shape == up.shape and gate.numel() % 8 == 0
             and gate.device.index == torch.cuda.current_device()):
         return None
-    check("sift_silu_mul", lib().sift_silu_mul(_ptr(gate), _ptr(up), gate.numel(), _ptr(gate),
-                                               _stream_ptr(stream)))
+    check("sift_layer_silu_mul", lib().sift_layer_silu_mul(
+        _ptr(gate), _ptr(up), gate.numel(), _ptr(gate), _stream_ptr(stream)))
     return gate
 
 

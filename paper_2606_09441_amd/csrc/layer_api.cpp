@@ -7,6 +7,7 @@
 
 #include <cstdint>
 
+#include "layer_api.h"
 #include "sift.h"
 #include "sift_internal.h"
 
@@ -33,8 +34,8 @@ sift_status sift_rope(const sift_tensor* q, const sift_tensor* k, const int32_t*
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }
 
-sift_status sift_rms_norm(const void* x, const void* weight, int64_t rows, int32_t width, float eps,
-                          void* out, void* stream) {
+sift_status sift_layer_rms_norm(const void* x, const void* weight, int64_t rows, int32_t width,
+                                float eps, void* out, void* stream) {
   if (rows < 0 || width < 1) return SIFT_E_SHAPE;
   if (rows == 0) return SIFT_OK;
   if (x == nullptr || weight == nullptr || out == nullptr) return SIFT_E_NULL;
@@ -46,8 +47,8 @@ sift_status sift_rms_norm(const void* x, const void* weight, int64_t rows, int32
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }
 
-sift_status sift_silu_mul(const void* gate, const void* up, int64_t count, void* out,
-                          void* stream) {
+sift_status sift_layer_silu_mul(const void* gate, const void* up, int64_t count, void* out,
+                                void* stream) {
   if (count < 0) return SIFT_E_SHAPE;
   if (count == 0) return SIFT_OK;
   if (gate == nullptr || up == nullptr || out == nullptr) return SIFT_E_NULL;
