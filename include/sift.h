@@ -379,9 +379,10 @@ size_t sift_static_scratch_bytes(void);
  *   0 <= gamma <= 1; softmax_scale <= 0 means 1/sqrt(D).  la_out, ca_out
  *   (device) receive the bit vectors; workspace (device, at least the size
  *   from sift_extract_sizes, 256-byte aligned) is scratch owned by the
- *   caller.  The call waits for `stream`, uploads its tables to the workspace
- *   synchronously, then enqueues the kernels on `stream` and returns.
- *   Calls that share a workspace must be ordered.
+ *   caller.  The tables are copied into the workspace on `stream` from pinned
+ *   host memory the library keeps, the kernels are enqueued on `stream`, and
+ *   the call returns without waiting.  Calls that share a workspace must be
+ *   ordered; a capturing stream is refused (SIFT_E_HIP).
  * Errors: SIFT_E_NULL, SIFT_E_LAYOUT (offsets), SIFT_E_SHAPE (tensors vs
  *   offsets, Hq % Hkv), SIFT_E_UNSUPPORTED (dtype, D, T, thresholds),
  *   SIFT_E_CAPACITY (workspace too small), SIFT_E_HIP.

@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 #include <vector>
 
 #include "sift.h"
@@ -120,13 +121,17 @@ sift_status sift_extract_bits(const sift_tensor* q, const sift_tensor* k, int32_
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint8_t* ws = static_cast<uint8_t*>(workspace);
-  // the workspace may still be read by earlier work on the stream
-  if (hipStreamSynchronize(s) != hipSuccess) return SIFT_E_HIP;
-  if (hipMemcpy(ws + ep.o_docs, ep.docs.data(), ep.docs.size() * sizeof(sift::ExtractDoc),
-                hipMemcpyHostToDevice) != hipSuccess)
+  // the tables come from memory that other calls reuse: not under capture
+  hipStreamCaptureStatus capture;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
     return SIFT_E_HIP;
-  if (hipMemcpy(ws + ep.o_blocks, ep.blocks.data(), ep.blocks.size() * sizeof(int32_t),
-                hipMemcpyHostToDevice) != hipSuccess)
+  const size_t docs_n = ep.docs.size() * sizeof(sift::ExtractDoc);
+  const size_t blocks_n = ep.blocks.size() * sizeof(int32_t);
+  if (sift::upload_staged(ws + ep.o_docs, ep.o_blocks + blocks_n - ep.o_docs, s,
+                          [&](uint8_t* out) {
+                            std::memcpy(out, ep.docs.data(), docs_n);
+                            std::memcpy(out + ep.o_blocks - ep.o_docs, ep.blocks.data(), blocks_n);
+                          }) != hipSuccess)
     return SIFT_E_HIP;
 
   sift::ExtractArgs a;

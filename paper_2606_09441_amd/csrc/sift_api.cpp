@@ -8,7 +8,10 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <deque>
+#include <functional>
 #include <limits>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <numeric>
@@ -81,24 +84,103 @@ sift_status check_io(const sift_tensor* q, const sift_tensor* k, const sift_tens
   return SIFT_OK;
 }
 
-// Host tables of a validated layout.
+// Host tables of a validated layout.  The records per query head (list units,
+// work units) are kept once per group, a run of M-blocks that every head has a
+// unit of; write_unit_records, write_work_records and write_splits make the
+// whole arrays, straight into the upload's memory.
+struct Group {
+  int32_t m0, nb, seg;
+  bool query;
+  int64_t cost;   // causal tiles of the group's last M-block: the union's length bound
+  int64_t parts;  // pieces
+  int64_t len;    // steps of a piece
+  sift::WorkRec rec;  // its work units' records, but for the heads, slot and first step
+};
+
+// A write record of a group; its head, first step and first work unit open.
+struct Part {
+  sift::UnitRec rec;
+  int64_t cost;       // tiles walked
+  int64_t off, work;  // the group's first step and work unit, of one head
+  int64_t unit_cost;
+};
+
 struct HostPlan {
   std::vector<int32_t> seg_tile0, seg_pages, seg_kind, seg_first, seg_la_off, seg_ca_off;
   std::vector<int32_t> tile_seg, tile_tok0, tile_len, tile_lo;
   std::vector<int32_t> tile_info;  // int4 per tile (see PlanTables::tile_info)
-  std::vector<int32_t> unit_head, unit_m0, unit_nb, step_off;  // list units
-  std::vector<int32_t> lu_work0, lu_nwork, lu_len;
-  std::vector<sift::UnitRec> urec;  // list units by descending cost (the decode write order)
-  std::vector<int32_t> wk_head, wk_m0, wk_nb, wk_off, wk_slot;        // work units
-  std::vector<int32_t> splits;  // int4 records (see WorkTables)
-  std::vector<sift::WorkRec> rec;     // work units in locality order
-  std::vector<sift::WorkRec> launch;  // launch slots, initially empty
+  std::vector<Group> groups;  // in locality order
+  std::vector<Part> parts;    // longest walk first
+  int32_t hkv = 0, group_heads = 0;
+  int64_t num_units = 0;    // list units
+  int64_t num_urec = 0;     // records of the decode write pass
+  int64_t num_work = 0;     // work units
+  int64_t num_splits = 0;   // split units
+  int64_t head_steps = 0, head_work = 0;  // bound of the steps, and work units, of one head
+  int64_t step_cap = 0;     // bound of all list units' steps
   int64_t chunk_size = 0;
   int64_t part_slots = 0;
   int64_t dense_tiles = 0;  // causal tiles of all prompts, one head
   int64_t la_bytes = 0, ca_bytes = 0;
   int32_t num_tokens = 0, num_segments = 0, num_tiles = 0;
 };
+
+// The list units' records in decode write order: longest walk first over all
+// heads, units of one length in locality order.
+void write_unit_records(const HostPlan& hp, sift::UnitRec* out) {
+  const int64_t g = hp.group_heads;
+  for (size_t i0 = 0; i0 < hp.parts.size();) {
+    size_t i1 = i0;
+    while (i1 < hp.parts.size() && hp.parts[i1].cost == hp.parts[i0].cost) ++i1;
+    for (int32_t kv = 0; kv < hp.hkv; ++kv)
+      for (size_t i = i0; i < i1; ++i)
+        for (int64_t j = 0; j < g; ++j) {
+          const Part& x = hp.parts[i];
+          sift::UnitRec r = x.rec;
+          r.head = static_cast<int32_t>(kv * g + j);
+          r.step_off = static_cast<int32_t>(g * (kv * hp.head_steps + x.off) + j * x.unit_cost);
+          r.work0 = static_cast<int32_t>(g * (kv * hp.head_work + x.work) + j * x.rec.nwork);
+          *out++ = r;
+        }
+    i0 = i1;
+  }
+}
+
+// The work units' records in locality order (work unit w is record w); the
+// launch order is made on the device after each decode, from the step counts.
+void write_work_records(const HostPlan& hp, sift::WorkRec* out) {
+  int64_t slot = 0, off = 0;
+  for (int32_t kv = 0; kv < hp.hkv; ++kv)
+    for (const Group& x : hp.groups)
+      for (int32_t j = 0; j < hp.group_heads; ++j) {
+        for (int64_t i = 0; i < x.parts; ++i) {
+          sift::WorkRec r = x.rec;
+          r.head = kv * hp.group_heads + j;
+          r.kv_head = kv;
+          r.slot = x.parts > 1 ? static_cast<int32_t>(slot++) : -1;
+          r.step_off = static_cast<int32_t>(off + i * x.len);
+          *out++ = r;
+        }
+        off += x.cost;
+      }
+}
+
+// The split units, int4 {record of the first piece, first slot, slots, 0}.
+void write_splits(const HostPlan& hp, int32_t* out) {
+  int64_t slot = 0, w = 0;
+  for (int32_t kv = 0; kv < hp.hkv; ++kv)
+    for (const Group& x : hp.groups)
+      for (int32_t j = 0; j < hp.group_heads; ++j) {
+        if (x.parts > 1) {
+          const int32_t r[4] = {static_cast<int32_t>(w), static_cast<int32_t>(slot),
+                                static_cast<int32_t>(x.parts), 0};
+          std::memcpy(out, r, sizeof(r));
+          out += 4;
+          slot += x.parts;
+        }
+        w += x.parts;
+      }
+}
 
 sift_status build_host_plan(const sift_layout* lay, int32_t hq, int32_t hkv, int32_t tile,
                             HostPlan& hp) {
@@ -190,17 +272,14 @@ sift_status build_host_plan(const sift_layout* lay, int32_t hq, int32_t hkv, int
   const int32_t halves = tile == 128 ? 2 : 1;
   const int32_t ub = tile == 128 ? 1 : sift::kUnitRows / tile;
   const int32_t G = tile < 64 ? 64 / tile : 1;
-  struct Group {
-    int32_t m0, nb;
-    int64_t cost;  // causal tiles of the group's last M-block: the union's length bound
-  };
-  std::vector<Group> groups;
+  std::vector<Group>& groups = hp.groups;
   for (int32_t s = 0; s < S; ++s) {
     const int32_t lo = hp.seg_tile0[hp.seg_first[s]];  // first tile of the prompt
     for (int32_t p = 0; p < hp.seg_pages[s]; p += ub) {
       const int32_t m0 = hp.seg_tile0[s] + p;
       const int32_t nb = std::min<int32_t>(ub, hp.seg_pages[s] - p);
-      groups.push_back({m0, nb, (m0 + nb - 1 - lo + 1) * halves});
+      groups.push_back({m0, nb, s, hp.seg_kind[s] == sift::kQuery,
+                        static_cast<int64_t>(m0 + nb - 1 - lo + 1) * halves, 1, 0, {}});
     }
   }
   // Units in locality order: kv head, then longest group first, then the
@@ -214,46 +293,20 @@ sift_status build_host_plan(const sift_layout* lay, int32_t hq, int32_t hkv, int
   // 2427 / 1468; 16,640 tokens, 4/1 204 / 134, 8/2 262 / 196, 24/3 653 / 501;
   // 4,224 tokens, 8/1 60 / 57.  A multiple of 8 kv heads needs no deal.
   const int32_t g = hq / hkv;
-  std::vector<int32_t> gord(groups.size());
-  std::iota(gord.begin(), gord.end(), 0);
-  std::stable_sort(gord.begin(), gord.end(),
-                   [&](int32_t x, int32_t y) { return groups[x].cost > groups[y].cost; });
+  std::stable_sort(groups.begin(), groups.end(),
+                   [](const Group& x, const Group& y) { return x.cost > y.cost; });
   const int64_t U = static_cast<int64_t>(groups.size()) * hq;
   if (U > i32max / 2) return SIFT_E_CAPACITY;
-  std::vector<int32_t> order;  // unit ids
-  order.reserve(U);
-  hp.unit_head.resize(U);
-  hp.unit_m0.resize(U);
-  hp.unit_nb.resize(U);
-  std::vector<int64_t> unit_cost(U);
-  int32_t u = 0;
   const int32_t runs = sift::kNumXcd / std::gcd(sift::kNumXcd, hkv);
   if (runs > 1) {
-    std::vector<int32_t> dealt;
-    dealt.reserve(gord.size());
+    std::vector<Group> dealt;
+    dealt.reserve(groups.size());
     for (int32_t r = 0; r < runs; ++r)
-      for (size_t i = 0; i < gord.size(); ++i) {
+      for (size_t i = 0; i < groups.size(); ++i) {
         const int32_t at = static_cast<int32_t>(i % (2 * runs));
-        if ((at < runs ? at : 2 * runs - 1 - at) == r) dealt.push_back(gord[i]);
+        if ((at < runs ? at : 2 * runs - 1 - at) == r) dealt.push_back(groups[i]);
       }
-    gord.swap(dealt);
-  }
-  for (int32_t kv = 0; kv < hkv; ++kv)
-    for (int32_t gi : gord)
-      for (int32_t j = 0; j < g; ++j) {
-        hp.unit_head[u] = kv * g + j;
-        hp.unit_m0[u] = groups[gi].m0;
-        hp.unit_nb[u] = groups[gi].nb;
-        unit_cost[u] = groups[gi].cost;
-        order.push_back(u);
-        ++u;
-      }
-  // A unit's merged list is a subset of the tiles from the prompt's first
-  // to its last M-block.
-  hp.step_off.assign(U + 1, 0);
-  for (int64_t k = 0; k < U; ++k) {
-    if (hp.step_off[k] + unit_cost[k] > i32max) return SIFT_E_CAPACITY;
-    hp.step_off[k + 1] = hp.step_off[k] + static_cast<int32_t>(unit_cost[k]);
+    groups.swap(dealt);
   }
   // Work units.  A query unit lists every tile of its prompt up to its last
   // M-block, so its list length is its cost.  The launch runs the longest
@@ -266,152 +319,122 @@ sift_status build_host_plan(const sift_layout* lay, int32_t hq, int32_t hkv, int
   constexpr int64_t kMaxSlots = 4096;
   constexpr int64_t kMinPiece = 32;
   constexpr int64_t kSlots = 512;  // 256 CUs x 2 resident attention workgroups
-  auto is_query = [&](int64_t k) { return hp.seg_kind[hp.tile_seg[hp.unit_m0[k]]] == sift::kQuery; };
-  int64_t lower = 0;
-  for (int64_t k = 0; k < U; ++k) lower += is_query(k) ? unit_cost[k] : hp.unit_nb[k];
+  int64_t lower = 0, steps = 0;
+  for (const Group& x : groups) {
+    lower += hq * (x.query ? x.cost : x.nb);
+    steps += hq * x.cost;
+    if (steps > i32max) return SIFT_E_CAPACITY;
+  }
+  hp.num_units = U;
+  hp.step_cap = steps;
   int64_t piece = std::max<int64_t>(kMinPiece, (lower + kSlots - 1) / kSlots);
   auto slots_for = [&](int64_t pc) {
     int64_t n = 0;
-    for (int64_t k = 0; k < U; ++k)
-      if (is_query(k) && unit_cost[k] > pc) n += (unit_cost[k] + pc - 1) / pc;
+    for (const Group& x : groups)
+      if (x.query && x.cost > pc) n += hq * ((x.cost + pc - 1) / pc);
     return n;
   };
   while (slots_for(piece) > kMaxSlots) piece *= 2;
-  hp.lu_work0.assign(U, 0);
-  hp.lu_nwork.assign(U, 1);
-  hp.lu_len.assign(U, 0);
-  int64_t W = 0;
-  for (int32_t uu : order) {
-    const int64_t cost = unit_cost[uu];
-    const int64_t parts = is_query(uu) && cost > piece ? (cost + piece - 1) / piece : 1;
-    const int64_t len = (cost + parts - 1) / parts;
-    hp.lu_work0[uu] = static_cast<int32_t>(hp.wk_head.size());
-    hp.lu_nwork[uu] = static_cast<int32_t>(parts);
-    hp.lu_len[uu] = static_cast<int32_t>(len);
-    if (parts > 1)
-      hp.splits.insert(hp.splits.end(), {static_cast<int32_t>(hp.wk_head.size()),
-                                         static_cast<int32_t>(hp.part_slots),
-                                         static_cast<int32_t>(parts), 0});
-    for (int64_t i = 0; i < parts; ++i) {
-      ++W;
-      hp.wk_head.push_back(hp.unit_head[uu]);
-      hp.wk_m0.push_back(hp.unit_m0[uu]);
-      hp.wk_nb.push_back(hp.unit_nb[uu]);
-      hp.wk_off.push_back(static_cast<int32_t>(hp.step_off[uu] + i * len));
-      hp.wk_slot.push_back(parts > 1 ? static_cast<int32_t>(hp.part_slots + i) : -1);
+  int64_t work = 0, split = 0;  // of one head: work units, partial slots
+  hp.num_splits = 0;
+  for (Group& x : groups) {
+    x.parts = x.query && x.cost > piece ? (x.cost + piece - 1) / piece : 1;
+    x.len = (x.cost + x.parts - 1) / x.parts;
+    work += x.parts;
+    if (x.parts > 1) {
+      split += x.parts;
+      hp.num_splits += hq;
     }
-    if (parts > 1) hp.part_slots += parts;
   }
+  const int64_t W = work * hq;
   if (W > i32max / 2) return SIFT_E_CAPACITY;
+  hp.num_work = W;
+  hp.part_slots = split * hq;
+  hp.hkv = hkv;
+  hp.group_heads = g;
+  hp.head_steps = hq > 0 ? steps / hq : 0;
+  hp.head_work = work;
   // Records of the decode write pass: one per unit, except that at T < 64 a
   // query unit's walk (segment by segment over its prompt, in steps of G
   // adjacent tiles) is cut into parts of whole segments of about kPartTiles
   // tiles, one wavefront each.  They run longest walk first over all heads,
   // so that no long walk starts late.
   constexpr int64_t kPartTiles = 256;
-  std::vector<int64_t> rcost;
-  for (int64_t uu = 0; uu < U; ++uu) {
-    const int32_t m0 = hp.unit_m0[uu], sg = hp.tile_seg[m0];
-    const bool query = hp.seg_kind[sg] == sift::kQuery;
-    sift::UnitRec r{};
-    r.head = hp.unit_head[uu];
-    r.m0 = m0;
-    r.nb = hp.unit_nb[uu];
-    r.seg = sg;
-    r.lo = hp.tile_lo[m0];
-    r.sd0 = hp.seg_tile0[sg];
-    r.pages = hp.seg_pages[sg];
-    r.la_off = hp.seg_la_off[sg];
-    r.step_off = hp.step_off[uu];
-    r.work0 = hp.lu_work0[uu];
-    r.nwork = hp.lu_nwork[uu];
-    r.plen = hp.lu_len[uu];
-    r.flags = (query ? sift::kUnitQuery : 0) | ((hp.tile_len[m0] > 64 ? 3 : 1) << 1);
-    r.part_d0 = hp.seg_first[sg];
-    r.part_d1 = sg + 1;
-    r.part_skip = 0;
-    if (!(query && G > 1)) {
-      r.flags |= sift::kUnitFirstPart | sift::kUnitLastPart;
-      hp.urec.push_back(r);
-      rcost.push_back(unit_cost[uu]);
-      continue;
-    }
-    // segment d's tiles walked by the unit, and its steps (groups of G)
-    const int32_t mlast = m0 + r.nb - 1;
-    auto tiles = [&](int32_t d) { return d < sg ? hp.seg_pages[d] : mlast - hp.seg_tile0[sg] + 1; };
-    int32_t skip = 0;
-    for (int32_t d0 = r.part_d0; d0 <= sg;) {
-      int32_t d1 = d0;
-      int64_t t = 0, g = 0;
-      while (d1 <= sg && (d1 == d0 || t + tiles(d1) <= kPartTiles)) {
-        t += tiles(d1);
-        g += (tiles(d1) + G - 1) / G;
-        ++d1;
-      }
-      sift::UnitRec p = r;
-      p.part_d0 = d0;
-      p.part_d1 = d1;
-      p.part_skip = skip;
-      if (d0 == r.part_d0) p.flags |= sift::kUnitFirstPart;
-      if (d1 == sg + 1) p.flags |= sift::kUnitLastPart;
-      hp.urec.push_back(p);
-      rcost.push_back(t);
-      skip += static_cast<int32_t>(g);
-      d0 = d1;
-    }
-  }
+  std::vector<Part>& parts = hp.parts;
   {
-    std::vector<int32_t> ro(hp.urec.size());
-    std::iota(ro.begin(), ro.end(), 0);
-    std::stable_sort(ro.begin(), ro.end(), [&](int32_t x, int32_t y) { return rcost[x] > rcost[y]; });
-    std::vector<sift::UnitRec> sorted(hp.urec.size());
-    for (size_t q = 0; q < ro.size(); ++q) sorted[q] = hp.urec[ro[q]];
-    hp.urec.swap(sorted);
-  }
-  if (hp.urec.size() > static_cast<size_t>(i32max / 2)) return SIFT_E_CAPACITY;
-  // Work-unit records in locality order (work unit w is record w); the
-  // launch order is made on the device after each decode, from the step
-  // counts.
-  hp.rec.assign(W, sift::WorkRec{});
-  for (int64_t w = 0; w < W; ++w) {
-    sift::WorkRec& r = hp.rec[w];
-    r.head = hp.wk_head[w];
-    r.kv_head = hp.wk_head[w] / (hq / hkv);
-    r.slot = hp.wk_slot[w];
-    if (halves == 1) {
-      // kernel block b: M-blocks m0 + G b .. m0 + G b + G - 1 of the unit
-      const int32_t m0 = hp.wk_m0[w], nb = hp.wk_nb[w];
-      const int32_t blocks = (nb + G - 1) / G;
-      for (int b = 0; b < blocks; ++b) {
-        r.tok0[b] = hp.tile_tok0[m0 + G * b];
-        r.len[b] = 0;
-        for (int32_t m = m0 + G * b; m < std::min(m0 + nb, m0 + G * b + G); ++m)
-          r.len[b] += hp.tile_len[m];
+    int64_t off = 0, w0 = 0;
+    for (Group& x : groups) {
+      const int32_t m0 = x.m0, sg = x.seg;
+      sift::UnitRec r{};
+      r.m0 = m0;
+      r.nb = x.nb;
+      r.seg = sg;
+      r.lo = hp.tile_lo[m0];
+      r.sd0 = hp.seg_tile0[sg];
+      r.pages = hp.seg_pages[sg];
+      r.la_off = hp.seg_la_off[sg];
+      r.nwork = static_cast<int32_t>(x.parts);
+      r.plen = static_cast<int32_t>(x.len);
+      r.flags = (x.query ? sift::kUnitQuery : 0) | ((hp.tile_len[m0] > 64 ? 3 : 1) << 1);
+      r.part_d0 = hp.seg_first[sg];
+      r.part_d1 = sg + 1;
+      r.part_skip = 0;
+      if (!(x.query && G > 1)) {
+        r.flags |= sift::kUnitFirstPart | sift::kUnitLastPart;
+        parts.push_back({r, x.cost, off, w0, x.cost});
+      } else {
+        // segment d's tiles walked by the unit, and its steps (groups of G)
+        const int32_t mlast = m0 + r.nb - 1;
+        auto tiles = [&](int32_t d) {
+          return d < sg ? hp.seg_pages[d] : mlast - hp.seg_tile0[sg] + 1;
+        };
+        int32_t skip = 0;
+        for (int32_t d0 = r.part_d0; d0 <= sg;) {
+          int32_t d1 = d0;
+          int64_t t = 0, n = 0;
+          while (d1 <= sg && (d1 == d0 || t + tiles(d1) <= kPartTiles)) {
+            t += tiles(d1);
+            n += (tiles(d1) + G - 1) / G;
+            ++d1;
+          }
+          sift::UnitRec p = r;
+          p.part_d0 = d0;
+          p.part_d1 = d1;
+          p.part_skip = skip;
+          if (d0 == r.part_d0) p.flags |= sift::kUnitFirstPart;
+          if (d1 == sg + 1) p.flags |= sift::kUnitLastPart;
+          parts.push_back({p, t, off, w0, x.cost});
+          skip += static_cast<int32_t>(n);
+          d0 = d1;
+        }
       }
-    } else {  // one M-block of T = 128: two kernel blocks of 64 rows
-      const int32_t m = hp.wk_m0[w], len = hp.tile_len[m];
-      r.tok0[0] = hp.tile_tok0[m];
-      r.len[0] = std::min<int32_t>(len, 64);
-      r.tok0[1] = len > 64 ? hp.tile_tok0[m] + 64 : 0;
-      r.len[1] = len > 64 ? len - 64 : 0;
+      off += x.cost;
+      w0 += x.parts;
+      sift::WorkRec& wr = x.rec;
+      if (halves == 1) {
+        // kernel block b: M-blocks m0 + G b .. m0 + G b + G - 1 of the unit
+        const int32_t blocks = (x.nb + G - 1) / G;
+        for (int b = 0; b < blocks; ++b) {
+          wr.tok0[b] = hp.tile_tok0[m0 + G * b];
+          wr.len[b] = 0;
+          for (int32_t m = m0 + G * b; m < std::min(m0 + x.nb, m0 + G * b + G); ++m)
+            wr.len[b] += hp.tile_len[m];
+        }
+      } else {  // one M-block of T = 128: two kernel blocks of 64 rows
+        const int32_t len = hp.tile_len[m0];
+        wr.tok0[0] = hp.tile_tok0[m0];
+        wr.len[0] = std::min<int32_t>(len, 64);
+        wr.tok0[1] = len > 64 ? hp.tile_tok0[m0] + 64 : 0;
+        wr.len[1] = len > 64 ? len - 64 : 0;
+      }
     }
-    r.step_off = hp.wk_off[w];
   }
-  // launch slots start empty (one M-block of no rows, no steps); the
-  // schedule pass fills those of the work units
+  hp.num_urec = static_cast<int64_t>(parts.size()) * hq;
+  if (hp.num_urec > i32max / 2) return SIFT_E_CAPACITY;
+  std::stable_sort(parts.begin(), parts.end(),
+                   [](const Part& x, const Part& y) { return x.cost > y.cost; });
   hp.chunk_size = (W + sift::kNumXcd - 1) / sift::kNumXcd;
-  sift::WorkRec empty{};
-  empty.slot = -1;
-  hp.launch.assign(hp.chunk_size * sift::kNumXcd, empty);
   return SIFT_OK;
-}
-
-template <class T>
-size_t put(std::vector<uint8_t>& blob, const std::vector<T>& v) {
-  const size_t off = (blob.size() + 255) & ~size_t(255);
-  blob.resize(off + v.size() * sizeof(T));
-  if (!v.empty()) std::memcpy(blob.data() + off, v.data(), v.size() * sizeof(T));
-  return off;
 }
 
 }  // namespace
@@ -439,7 +462,9 @@ namespace {
 // Pinned host staging for stream-ordered uploads of plan tables.  A buffer
 // is handed out to one call at a time; after the call has enqueued its copy
 // it records an event, and the buffer is reused once that event has
-// completed (the copy has read it).  Buffers live until the process ends.
+// completed (the copy has read it).  Buffers live until the process ends; a
+// call that finds kMaxStaging of them busy on its device waits for one of
+// those that are large enough rather than allocate another.
 struct StagingBuf {
   int device;
   void* host;
@@ -447,46 +472,84 @@ struct StagingBuf {
   hipEvent_t done;
   bool taken;
 };
+constexpr size_t kMaxStaging = 64;
 std::mutex g_staging_mu;
-std::vector<StagingBuf> g_staging;
+std::deque<StagingBuf> g_staging;  // references stay valid
 
-// Index of a free pinned buffer of at least n bytes on the current device.
-sift_status staging_acquire(size_t n, size_t* idx) {
+// A pinned buffer of at least n bytes on the current device, not in use.
+sift_status staging_acquire(size_t n, StagingBuf** out) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return SIFT_E_HIP;
-  std::lock_guard<std::mutex> lock(g_staging_mu);
-  for (size_t i = 0; i < g_staging.size(); ++i) {
-    StagingBuf& b = g_staging[i];
-    if (b.taken || b.device != dev || b.cap < n) continue;
-    const hipError_t q = hipEventQuery(b.done);
-    if (q == hipErrorNotReady) continue;
-    if (q != hipSuccess) return SIFT_E_HIP;
-    b.taken = true;
-    *idx = i;
-    return SIFT_OK;
+  StagingBuf* busy = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(g_staging_mu);
+    size_t held = 0;
+    for (StagingBuf& b : g_staging) {
+      held += b.device == dev ? 1 : 0;
+      if (b.taken || b.device != dev || b.cap < n) continue;
+      const hipError_t q = hipEventQuery(b.done);
+      if (q == hipErrorNotReady) {
+        if (busy == nullptr) busy = &b;
+        continue;
+      }
+      if (q != hipSuccess) return SIFT_E_HIP;
+      b.taken = true;
+      *out = &b;
+      return SIFT_OK;
+    }
+    if (held >= kMaxStaging && busy != nullptr) {
+      busy->taken = true;
+    } else {
+      busy = nullptr;
+      size_t cap = 1 << 16;
+      while (cap < n) cap <<= 1;
+      StagingBuf b{dev, nullptr, cap, nullptr, true};
+      if (hipHostMalloc(&b.host, cap, hipHostMallocDefault) != hipSuccess) return SIFT_E_HIP;
+      if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
+        (void)hipHostFree(b.host);
+        return SIFT_E_HIP;
+      }
+      g_staging.push_back(b);
+      *out = &g_staging.back();
+      return SIFT_OK;
+    }
   }
-  size_t cap = 1 << 16;
-  while (cap < n) cap <<= 1;
-  StagingBuf b{dev, nullptr, cap, nullptr, true};
-  if (hipHostMalloc(&b.host, cap, hipHostMallocDefault) != hipSuccess) return SIFT_E_HIP;
-  if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
-    (void)hipHostFree(b.host);
+  if (hipEventSynchronize(busy->done) != hipSuccess) {
+    std::lock_guard<std::mutex> lock(g_staging_mu);
+    busy->taken = false;
     return SIFT_E_HIP;
   }
-  g_staging.push_back(b);
-  *idx = g_staging.size() - 1;
+  *out = busy;
   return SIFT_OK;
 }
 
-// Hand a buffer back; with a stream, once the copies enqueued on it so far
-// are done.
-sift_status staging_release(size_t idx, hipStream_t stream, bool record) {
+// Hand a buffer back; with record, once the copies enqueued on the stream so
+// far are done.
+sift_status staging_release(StagingBuf* b, hipStream_t stream, bool record) {
   std::lock_guard<std::mutex> lock(g_staging_mu);
-  StagingBuf& b = g_staging[idx];
-  b.taken = false;
-  if (record && hipEventRecord(b.done, stream) != hipSuccess) return SIFT_E_HIP;
+  b->taken = false;
+  if (record && hipEventRecord(b->done, stream) != hipSuccess) return SIFT_E_HIP;
   return SIFT_OK;
 }
+
+}  // namespace
+
+namespace sift {
+
+hipError_t upload_staged(void* dst, size_t n, hipStream_t stream,
+                         const std::function<void(uint8_t*)>& fill) {
+  StagingBuf* b = nullptr;
+  if (staging_acquire(n, &b) != SIFT_OK) return hipErrorUnknown;
+  fill(static_cast<uint8_t*>(b->host));
+  const hipError_t e = hipMemcpyAsync(dst, b->host, n, hipMemcpyHostToDevice, stream);
+  if (staging_release(b, stream, e == hipSuccess) != SIFT_OK && e == hipSuccess)
+    return hipErrorUnknown;
+  return e;
+}
+
+}  // namespace sift
+
+namespace {
 
 // How the plan's tables reach the device.
 enum class Upload {
@@ -496,82 +559,130 @@ enum class Upload {
                // `stream` (no allocation at all)
 };
 
-// The plan's device memory: with ws == nullptr a hipMalloc of its own, else
-// ws (ws_bytes, 256-byte aligned): the caller's workspace, stream-ordered
-// scratch or static scratch, written on `stream` as `up` says.  With
-// bytes_only != nullptr only the size is computed.
-//
-// Layout: the tables, then the schedule's bucket sizes and the attention's
+// A checked layout's tables, and where each goes in the plan's device memory:
+// the tables, then the schedule's bucket sizes and the attention's
 // redo flag (zero: uploaded with the tables, and left so by every pass that
 // uses them), then the decode and merge scratch.
-sift_status create_plan(const sift_layout* layout, int32_t num_q_heads, int32_t num_kv_heads,
-                        int32_t head_dim, int32_t tile, void* ws, size_t ws_bytes,
-                        hipStream_t stream, Upload up, size_t* bytes_only,
-                        sift_plan** plan_out) {
-  if (layout == nullptr || (plan_out == nullptr && bytes_only == nullptr)) return SIFT_E_NULL;
-  if (plan_out != nullptr) *plan_out = nullptr;
+struct PlanImage {
+  HostPlan hp;
+  int32_t hq, hkv, head_dim, tile;
+  // byte offsets of the tables
+  size_t seg_tile0, seg_pages, seg_kind, seg_first, seg_la, seg_ca;
+  size_t tile_seg, tile_tok0, tile_len, tile_lo, tile_info;
+  size_t urec, rec, launch, splits, hist;
+  size_t upload;  // bytes of the tables
+  // of the scratch
+  size_t counts, segbase, headtot, camark, segcross, crosscol, crossrows, rowptr, col, steps, kvb;
+  size_t part_o, part_lo, part_ml;
+  size_t total;
+};
+
+// the schedule's bucket sizes, the bf16 attention's redo flag and counters,
+// the decode's finished-block count: zeros, uploaded with the tables
+constexpr size_t kHistWords = sift::kNumXcd * sift::kSchedBuckets + 4 + sift::kNumXcd;
+
+sift_status make_image(const sift_layout* layout, int32_t num_q_heads, int32_t num_kv_heads,
+                       int32_t head_dim, int32_t tile, PlanImage& im) {
+  if (layout == nullptr) return SIFT_E_NULL;
   if (num_q_heads < 1 || num_kv_heads < 1 || num_q_heads % num_kv_heads != 0) return SIFT_E_SHAPE;
   if (head_dim != 64 && head_dim != 128) return SIFT_E_UNSUPPORTED;
   if (tile != 16 && tile != 32 && tile != 64 && tile != 128) return SIFT_E_UNSUPPORTED;
-  HostPlan hp;
+  HostPlan& hp = im.hp;
   sift_status st = build_host_plan(layout, num_q_heads, num_kv_heads, tile, hp);
   if (st != SIFT_OK) return st;
-
-  std::vector<uint8_t> blob;
-  const size_t o_seg_tile0 = put(blob, hp.seg_tile0);
-  const size_t o_seg_pages = put(blob, hp.seg_pages);
-  const size_t o_seg_kind = put(blob, hp.seg_kind);
-  const size_t o_seg_first = put(blob, hp.seg_first);
-  const size_t o_seg_la = put(blob, hp.seg_la_off);
-  const size_t o_seg_ca = put(blob, hp.seg_ca_off);
-  const size_t o_tile_seg = put(blob, hp.tile_seg);
-  const size_t o_tile_tok0 = put(blob, hp.tile_tok0);
-  const size_t o_tile_len = put(blob, hp.tile_len);
-  const size_t o_tile_lo = put(blob, hp.tile_lo);
-  const size_t o_tile_info = put(blob, hp.tile_info);
-  const size_t o_urec = put(blob, hp.urec);
-  const size_t o_rec = put(blob, hp.rec);  // step counts and first steps: written by decode
-  const size_t o_launch = put(blob, hp.launch);  // written by the schedule pass
-  const size_t o_splits = put(blob, hp.splits);
-  // the schedule's bucket sizes, the bf16 attention's redo flag and
-  // counters, the decode's finished-block count: zeros, uploaded with the
-  // tables
-  constexpr size_t kHistWords = sift::kNumXcd * sift::kSchedBuckets + 4 + sift::kNumXcd;
-  const size_t o_hist = put(blob, std::vector<int32_t>(kHistWords, 0));
+  im.hq = num_q_heads;
+  im.hkv = num_kv_heads;
+  im.head_dim = head_dim;
+  im.tile = tile;
+  size_t at = 0;
+  auto place = [&at](size_t n) {
+    const size_t off = (at + 255) & ~size_t(255);
+    at = off + n;
+    return off;
+  };
+  auto ints = [&](const std::vector<int32_t>& v) { return place(v.size() * sizeof(int32_t)); };
+  im.seg_tile0 = ints(hp.seg_tile0);
+  im.seg_pages = ints(hp.seg_pages);
+  im.seg_kind = ints(hp.seg_kind);
+  im.seg_first = ints(hp.seg_first);
+  im.seg_la = ints(hp.seg_la_off);
+  im.seg_ca = ints(hp.seg_ca_off);
+  im.tile_seg = ints(hp.tile_seg);
+  im.tile_tok0 = ints(hp.tile_tok0);
+  im.tile_len = ints(hp.tile_len);
+  im.tile_lo = ints(hp.tile_lo);
+  im.tile_info = ints(hp.tile_info);
+  im.urec = place(hp.num_urec * sizeof(sift::UnitRec));
+  im.rec = place(hp.num_work * sizeof(sift::WorkRec));  // counts and first steps: by decode
+  im.launch = place(hp.chunk_size * sift::kNumXcd * sizeof(sift::WorkRec));  // by the schedule pass
+  im.splits = place(hp.num_splits * 4 * sizeof(int32_t));
+  im.hist = place(kHistWords * sizeof(int32_t));
+  im.upload = at;
   const int64_t rows = static_cast<int64_t>(hp.num_tiles) * num_q_heads;
+  const int64_t segs = static_cast<int64_t>(hp.num_segments) * num_q_heads;
   const int64_t cap = hp.dense_tiles * num_q_heads;
-  const int64_t U = static_cast<int64_t>(hp.unit_head.size());
-  auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
-  const size_t o_counts = align(blob.size());
-  const size_t o_segbase = align(o_counts + rows * 4);
-  const size_t o_headtot = align(o_segbase + static_cast<int64_t>(hp.num_segments) * num_q_heads * 4);
-  const size_t o_camark = align(o_headtot + static_cast<int64_t>(num_q_heads) * 4);
-  const size_t o_segcross = align(o_camark + rows);
-  const size_t o_crosscol =
-      align(o_segcross + static_cast<int64_t>(hp.num_segments) * num_q_heads * 4);
-  const size_t o_crossrows = align(o_crosscol + rows * 4);
-  const size_t o_rowptr = align(o_crossrows + rows * 8);
-  const size_t o_col = align(o_rowptr + (rows + 1) * 4);
-  const int64_t W = static_cast<int64_t>(hp.wk_head.size());
-  const size_t o_steps = align(o_col + std::max<int64_t>(cap, 1) * 4);
+  im.counts = place(rows * 4);
+  im.segbase = place(segs * 4);
+  im.headtot = place(static_cast<int64_t>(num_q_heads) * 4);
+  im.camark = place(rows);
+  im.segcross = place(segs * 4);
+  im.crosscol = place(rows * 4);
+  im.crossrows = place(rows * 8);
+  im.rowptr = place((rows + 1) * 4);
+  im.col = place(std::max<int64_t>(cap, 1) * 4);
   // steps: the units' lists, plus a few entries read (never used) past the end
   // (the lists' total length bound: one step per listed tile at T <= 64, up
-  // to two at T = 128)
-  const int64_t step_cap = hp.step_off.empty() ? 0 : hp.step_off.back();
-  // per-step K/V row bases, T < 64 only
-  const size_t o_kvb = align(o_steps + (std::max<int64_t>(step_cap, 1) + 8) * 8);
-  const size_t o_part_o =
-      align(o_kvb + (tile < 64 ? (std::max<int64_t>(step_cap, 1) + 8) * 16 : 0));
+  // to two at T = 128); per-step K/V row bases at T < 64 only
+  const int64_t step_room = std::max<int64_t>(hp.step_cap, 1) + 8;
+  im.steps = place(step_room * 8);
+  im.kvb = place(tile < 64 ? step_room * 16 : 0);
   const int64_t slot_rows = hp.part_slots * sift::kUnitRows;
   // the pieces' outputs: fp32, or bf16 plus the bf16 of its rounding error
-  const size_t o_part_lo = align(o_part_o + slot_rows * head_dim * 4);
-  const size_t o_part_ml = align(o_part_lo + slot_rows * head_dim * 2);
-  const size_t total = o_part_ml + std::max<int64_t>(slot_rows, 1) * 8;
+  im.part_o = place(slot_rows * head_dim * 4);
+  im.part_lo = place(slot_rows * head_dim * 2);
+  im.part_ml = place(std::max<int64_t>(slot_rows, 1) * 8);
+  im.total = at;
+  return SIFT_OK;
+}
 
-  if (bytes_only != nullptr) {
-    *bytes_only = total;
-    return SIFT_OK;
-  }
+// The tables, im.upload bytes.
+void write_tables(const PlanImage& im, uint8_t* out) {
+  const HostPlan& hp = im.hp;
+  auto ints = [out](size_t off, const std::vector<int32_t>& v) {
+    if (!v.empty()) std::memcpy(out + off, v.data(), v.size() * sizeof(int32_t));
+  };
+  ints(im.seg_tile0, hp.seg_tile0);
+  ints(im.seg_pages, hp.seg_pages);
+  ints(im.seg_kind, hp.seg_kind);
+  ints(im.seg_first, hp.seg_first);
+  ints(im.seg_la, hp.seg_la_off);
+  ints(im.seg_ca, hp.seg_ca_off);
+  ints(im.tile_seg, hp.tile_seg);
+  ints(im.tile_tok0, hp.tile_tok0);
+  ints(im.tile_len, hp.tile_len);
+  ints(im.tile_lo, hp.tile_lo);
+  ints(im.tile_info, hp.tile_info);
+  write_unit_records(hp, reinterpret_cast<sift::UnitRec*>(out + im.urec));
+  write_work_records(hp, reinterpret_cast<sift::WorkRec*>(out + im.rec));
+  // launch slots start empty (one M-block of no rows, no steps); the
+  // schedule pass fills those of the work units
+  sift::WorkRec empty{};
+  empty.slot = -1;
+  std::fill_n(reinterpret_cast<sift::WorkRec*>(out + im.launch), hp.chunk_size * sift::kNumXcd,
+              empty);
+  write_splits(hp, reinterpret_cast<int32_t*>(out + im.splits));
+  std::memset(out + im.hist, 0, kHistWords * sizeof(int32_t));
+}
+
+// The plan of an image.  Its device memory: with ws == nullptr a hipMalloc of
+// its own, else ws (ws_bytes, 256-byte aligned): the caller's workspace,
+// stream-ordered scratch or static scratch, written on `stream` as `up` says.
+sift_status create_plan(const PlanImage& im, void* ws, size_t ws_bytes, hipStream_t stream,
+                        Upload up, sift_plan** plan_out) {
+  if (plan_out == nullptr) return SIFT_E_NULL;
+  *plan_out = nullptr;
+  const HostPlan& hp = im.hp;
+  const size_t total = im.total;
   if (ws != nullptr) {
     if (ws_bytes < total) return SIFT_E_CAPACITY;
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return SIFT_E_UNSUPPORTED;
@@ -588,93 +699,95 @@ sift_status create_plan(const sift_layout* layout, int32_t num_q_heads, int32_t 
     return SIFT_E_HIP;
   };
   plan->dev_bytes = total;
-  if (ws == nullptr) {
-    if (hipMalloc(&plan->dev, total) != hipSuccess) return fail();
-    if (hipMemcpy(plan->dev, blob.data(), blob.size(), hipMemcpyHostToDevice) != hipSuccess)
-      return fail();
-  } else {
+  if (ws != nullptr) {
     plan->dev = ws;
     plan->owns_dev = false;
     plan->last_stream = stream;
-    if (up == Upload::kStaged) {
-      // copy from pinned staging: the call returns without waiting, and the
-      // staging buffer is reused only after the copy has read it
-      size_t idx = 0;
-      if (staging_acquire(blob.size(), &idx) != SIFT_OK) return fail();
-      std::memcpy(g_staging[idx].host, blob.data(), blob.size());
-      const bool ok = hipMemcpyAsync(plan->dev, g_staging[idx].host, blob.size(),
-                                     hipMemcpyHostToDevice, stream) == hipSuccess;
-      if (staging_release(idx, stream, ok) != SIFT_OK || !ok) return fail();
-    } else {
-      // host memory: the blob must outlive the copy, so wait for the stream
-      if (hipMemcpyAsync(plan->dev, blob.data(), blob.size(), hipMemcpyHostToDevice,
-                         stream) != hipSuccess)
+  } else if (hipMalloc(&plan->dev, total) != hipSuccess) {
+    return fail();
+  }
+  if (up == Upload::kStaged) {
+    // from pinned staging: the call returns without waiting
+    if (sift::upload_staged(plan->dev, im.upload, stream,
+                            [&im](uint8_t* out) { write_tables(im, out); }) != hipSuccess)
+      return fail();
+  } else {
+    std::unique_ptr<uint8_t[]> host(new (std::nothrow) uint8_t[im.upload]);
+    if (host == nullptr) return fail();
+    write_tables(im, host.get());
+    if (up == Upload::kBlocking) {
+      if (hipMemcpy(plan->dev, host.get(), im.upload, hipMemcpyHostToDevice) != hipSuccess)
         return fail();
-      if (hipStreamSynchronize(stream) != hipSuccess) return fail();
+    } else {
+      // host memory: it must outlive the copy, so wait for the stream
+      if (hipMemcpyAsync(plan->dev, host.get(), im.upload, hipMemcpyHostToDevice, stream) !=
+              hipSuccess ||
+          hipStreamSynchronize(stream) != hipSuccess)
+        return fail();
     }
   }
   auto P = [plan](size_t off) {
     return reinterpret_cast<int32_t*>(static_cast<uint8_t*>(plan->dev) + off);
   };
-  plan->pt.seg_tile0 = P(o_seg_tile0);
-  plan->pt.seg_pages = P(o_seg_pages);
-  plan->pt.seg_kind = P(o_seg_kind);
-  plan->pt.seg_first = P(o_seg_first);
-  plan->pt.seg_la_off = P(o_seg_la);
-  plan->pt.seg_ca_off = P(o_seg_ca);
-  plan->pt.tile_seg = P(o_tile_seg);
-  plan->pt.tile_tok0 = P(o_tile_tok0);
-  plan->pt.tile_len = P(o_tile_len);
-  plan->pt.tile_lo = P(o_tile_lo);
-  plan->pt.tile_info = reinterpret_cast<const int4*>(P(o_tile_info));
-  plan->pt.tile = tile;
-  plan->pt.halves = tile == 128 ? 2 : 1;
-  plan->pt.group = tile < 64 ? 64 / tile : 1;
+  plan->pt.seg_tile0 = P(im.seg_tile0);
+  plan->pt.seg_pages = P(im.seg_pages);
+  plan->pt.seg_kind = P(im.seg_kind);
+  plan->pt.seg_first = P(im.seg_first);
+  plan->pt.seg_la_off = P(im.seg_la);
+  plan->pt.seg_ca_off = P(im.seg_ca);
+  plan->pt.tile_seg = P(im.tile_seg);
+  plan->pt.tile_tok0 = P(im.tile_tok0);
+  plan->pt.tile_len = P(im.tile_len);
+  plan->pt.tile_lo = P(im.tile_lo);
+  plan->pt.tile_info = reinterpret_cast<const int4*>(P(im.tile_info));
+  plan->pt.tile = im.tile;
+  plan->pt.halves = im.tile == 128 ? 2 : 1;
+  plan->pt.group = im.tile < 64 ? 64 / im.tile : 1;
   plan->pt.num_tiles = hp.num_tiles;
   plan->pt.num_segments = hp.num_segments;
-  plan->pt.num_q_heads = num_q_heads;
-  plan->wt.rec = reinterpret_cast<sift::WorkRec*>(P(o_rec));
-  plan->wt.launch = reinterpret_cast<sift::WorkRec*>(P(o_launch));
-  plan->wt.hist = P(o_hist);
-  plan->wt.urec = reinterpret_cast<const sift::UnitRec*>(P(o_urec));
-  plan->wt.steps = reinterpret_cast<int2*>(P(o_steps));
-  plan->wt.kvb = tile < 64 ? reinterpret_cast<int4*>(P(o_kvb)) : nullptr;
-  plan->wt.splits = reinterpret_cast<const int4*>(P(o_splits));
-  plan->wt.part_o = static_cast<void*>(P(o_part_o));
-  plan->wt.part_lo = static_cast<void*>(P(o_part_lo));
-  plan->wt.part_ml = reinterpret_cast<float2*>(P(o_part_ml));
-  plan->wt.redo = P(o_hist) + sift::kNumXcd * sift::kSchedBuckets;
+  plan->pt.num_q_heads = im.hq;
+  plan->wt.rec = reinterpret_cast<sift::WorkRec*>(P(im.rec));
+  plan->wt.launch = reinterpret_cast<sift::WorkRec*>(P(im.launch));
+  plan->wt.hist = P(im.hist);
+  plan->wt.urec = reinterpret_cast<const sift::UnitRec*>(P(im.urec));
+  plan->wt.steps = reinterpret_cast<int2*>(P(im.steps));
+  plan->wt.kvb = im.tile < 64 ? reinterpret_cast<int4*>(P(im.kvb)) : nullptr;
+  plan->wt.splits = reinterpret_cast<const int4*>(P(im.splits));
+  plan->wt.part_o = static_cast<void*>(P(im.part_o));
+  plan->wt.part_lo = static_cast<void*>(P(im.part_lo));
+  plan->wt.part_ml = reinterpret_cast<float2*>(P(im.part_ml));
+  plan->wt.redo = P(im.hist) + sift::kNumXcd * sift::kSchedBuckets;
   plan->wt.decode_done = plan->wt.redo + 3;
   plan->wt.sched_done = plan->wt.redo + 4;
-  plan->wt.seg_base = P(o_segbase);
-  plan->wt.head_tot = P(o_headtot);
-  plan->wt.ca_mark = reinterpret_cast<uint8_t*>(P(o_camark));
-  plan->wt.seg_cross = P(o_segcross);
-  plan->wt.cross_col = P(o_crosscol);
-  plan->wt.cross_rows = reinterpret_cast<int2*>(P(o_crossrows));
-  plan->wt.num_units = static_cast<int32_t>(U);
-  plan->wt.num_urec = static_cast<int32_t>(hp.urec.size());
-  plan->wt.num_work = static_cast<int32_t>(W);
-  plan->wt.num_splits = static_cast<int32_t>(hp.splits.size() / 4);
+  plan->wt.seg_base = P(im.segbase);
+  plan->wt.head_tot = P(im.headtot);
+  plan->wt.ca_mark = reinterpret_cast<uint8_t*>(P(im.camark));
+  plan->wt.seg_cross = P(im.segcross);
+  plan->wt.cross_col = P(im.crosscol);
+  plan->wt.cross_rows = reinterpret_cast<int2*>(P(im.crossrows));
+  plan->wt.num_units = static_cast<int32_t>(hp.num_units);
+  plan->wt.num_urec = static_cast<int32_t>(hp.num_urec);
+  plan->wt.num_work = static_cast<int32_t>(hp.num_work);
+  plan->wt.num_splits = static_cast<int32_t>(hp.num_splits);
   plan->wt.chunk_size = static_cast<int32_t>(hp.chunk_size);
   plan->wt.sched_blocks = static_cast<int32_t>(
       std::min<int64_t>(8, std::max<int64_t>(1, ceil_div(hp.chunk_size, sift::kSchedPerBlock))));
-  plan->wt.grid = static_cast<int32_t>(hp.launch.size());
-  plan->counts = P(o_counts);
-  plan->row_ptr = P(o_rowptr);
-  plan->col_idx = P(o_col);
+  plan->wt.grid = static_cast<int32_t>(hp.chunk_size * sift::kNumXcd);
+  plan->counts = P(im.counts);
+  plan->row_ptr = P(im.rowptr);
+  plan->col_idx = P(im.col);
 
   sift_plan_info& in = plan->info;
   in.num_tokens = hp.num_tokens;
   in.num_segments = hp.num_segments;
   in.num_tiles = hp.num_tiles;
-  in.num_q_heads = num_q_heads;
-  in.num_kv_heads = num_kv_heads;
-  in.head_dim = head_dim;
-  in.tile = tile;
-  in.num_work_units = static_cast<int32_t>(W);
-  in.num_rows = rows;
-  in.list_capacity = cap;
+  in.num_q_heads = im.hq;
+  in.num_kv_heads = im.hkv;
+  in.head_dim = im.head_dim;
+  in.tile = im.tile;
+  in.num_work_units = static_cast<int32_t>(hp.num_work);
+  in.num_rows = static_cast<int64_t>(hp.num_tiles) * im.hq;
+  in.list_capacity = hp.dense_tiles * im.hq;
   in.la_bytes = hp.la_bytes;
   in.ca_bytes = hp.ca_bytes;
   in.scratch_bytes = static_cast<int64_t>(total);
@@ -683,24 +796,20 @@ sift_status create_plan(const sift_layout* layout, int32_t num_q_heads, int32_t 
 }
 
 // Arguments of the one-shot forms, checked on the host before anything is
-// enqueued; *need receives the scratch bytes of their plan.
+// enqueued; im receives the image of their plan.
 sift_status check_prefill(const sift_tensor* q, const sift_tensor* k, const sift_tensor* v,
                           const sift_layout* layout, const uint8_t* la, const uint8_t* ca,
-                          int32_t tile, const sift_tensor* out, size_t* need) {
+                          int32_t tile, const sift_tensor* out, PlanImage& im) {
   if (q == nullptr || k == nullptr || v == nullptr || out == nullptr || layout == nullptr)
     return SIFT_E_NULL;
   if (q->heads < 1 || k->heads < 1 || q->heads % k->heads != 0) return SIFT_E_SHAPE;
-  if (q->head_dim != 64 && q->head_dim != 128) return SIFT_E_UNSUPPORTED;
-  if (tile != 16 && tile != 32 && tile != 64 && tile != 128) return SIFT_E_UNSUPPORTED;
-  HostPlan hp;
-  sift_status st = build_host_plan(layout, q->heads, k->heads, tile, hp);
+  sift_status st = make_image(layout, q->heads, k->heads, q->head_dim, tile, im);
   if (st != SIFT_OK) return st;
-  st = check_io(q, k, v, out, hp.num_tokens, q->heads, k->heads, q->head_dim, tile);
+  st = check_io(q, k, v, out, im.hp.num_tokens, q->heads, k->heads, q->head_dim, tile);
   if (st != SIFT_OK) return st;
-  if (hp.la_bytes > 0 && la == nullptr) return SIFT_E_NULL;
-  if (hp.ca_bytes > 0 && ca == nullptr) return SIFT_E_NULL;
-  return create_plan(layout, q->heads, k->heads, q->head_dim, tile, nullptr, 0, nullptr,
-                     Upload::kBlocking, need, nullptr);
+  if (im.hp.la_bytes > 0 && la == nullptr) return SIFT_E_NULL;
+  if (im.hp.ca_bytes > 0 && ca == nullptr) return SIFT_E_NULL;
+  return SIFT_OK;
 }
 
 // Scratch for sift_sparse_prefill_static: one array per GPU, held from the
@@ -740,16 +849,21 @@ sift_status sift_plan_create(const sift_layout* layout, int32_t num_q_heads,
                              int32_t num_kv_heads, int32_t head_dim, int32_t tile,
                              sift_plan** plan_out) {
   if (plan_out == nullptr) return SIFT_E_NULL;
-  return create_plan(layout, num_q_heads, num_kv_heads, head_dim, tile, nullptr, 0, nullptr,
-                     Upload::kBlocking, nullptr, plan_out);
+  *plan_out = nullptr;
+  PlanImage im;
+  const sift_status st = make_image(layout, num_q_heads, num_kv_heads, head_dim, tile, im);
+  if (st != SIFT_OK) return st;
+  return create_plan(im, nullptr, 0, nullptr, Upload::kBlocking, plan_out);
 }
 
 sift_status sift_workspace_bytes(const sift_layout* layout, int32_t num_q_heads,
                                  int32_t num_kv_heads, int32_t head_dim, int32_t tile,
                                  size_t* bytes) {
   if (bytes == nullptr) return SIFT_E_NULL;
-  return create_plan(layout, num_q_heads, num_kv_heads, head_dim, tile, nullptr, 0, nullptr,
-                     Upload::kBlocking, bytes, nullptr);
+  PlanImage im;
+  const sift_status st = make_image(layout, num_q_heads, num_kv_heads, head_dim, tile, im);
+  if (st == SIFT_OK) *bytes = im.total;
+  return st;
 }
 
 sift_status sift_plan_destroy(sift_plan* plan) {
@@ -972,17 +1086,15 @@ sift_status sift_sparse_prefill(const sift_tensor* q, const sift_tensor* k, cons
                                 const sift_layout* doc_offsets, const uint8_t* local_bitmap,
                                 const uint8_t* cross_bitmap, int32_t tile, sift_tensor* out,
                                 void* stream) {
-  size_t need = 0;
-  sift_status st = check_prefill(q, k, v, doc_offsets, local_bitmap, cross_bitmap, tile, out,
-                                 &need);
+  PlanImage im;
+  sift_status st = check_prefill(q, k, v, doc_offsets, local_bitmap, cross_bitmap, tile, out, im);
   if (st != SIFT_OK) return st;
   // stream-ordered scratch: allocated, used and freed in the order of `stream`
   const hipStream_t s = static_cast<hipStream_t>(stream);
   void* ws = nullptr;
-  if (hipMallocAsync(&ws, need, s) != hipSuccess) return SIFT_E_HIP;
+  if (hipMallocAsync(&ws, im.total, s) != hipSuccess) return SIFT_E_HIP;
   sift_plan* plan = nullptr;
-  st = create_plan(doc_offsets, q->heads, k->heads, q->head_dim, tile, ws, need, s,
-                   Upload::kStaged, nullptr, &plan);
+  st = create_plan(im, ws, im.total, s, Upload::kStaged, &plan);
   if (st == SIFT_OK)
     st = sift_plan_run(plan, q, k, v, local_bitmap, cross_bitmap, 0.f, out, stream);
   const sift_status st2 = sift_plan_destroy(plan);  // host state only: ws is freed below
@@ -995,17 +1107,15 @@ sift_status sift_sparse_prefill_ex(const sift_tensor* q, const sift_tensor* k,
                                    const uint8_t* local_bitmap, const uint8_t* cross_bitmap,
                                    int32_t tile, float softmax_scale, void* workspace,
                                    size_t workspace_bytes, sift_tensor* out, void* stream) {
-  size_t need = 0;
-  sift_status st = check_prefill(q, k, v, doc_offsets, local_bitmap, cross_bitmap, tile, out,
-                                 &need);
+  PlanImage im;
+  sift_status st = check_prefill(q, k, v, doc_offsets, local_bitmap, cross_bitmap, tile, out, im);
   if (st != SIFT_OK) return st;
   if (workspace == nullptr) return SIFT_E_NULL;
-  if (workspace_bytes < need) return SIFT_E_CAPACITY;
+  if (workspace_bytes < im.total) return SIFT_E_CAPACITY;
   if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return SIFT_E_UNSUPPORTED;
   sift_plan* plan = nullptr;
-  st = create_plan(doc_offsets, q->heads, k->heads, q->head_dim, tile, workspace,
-                   workspace_bytes, static_cast<hipStream_t>(stream), Upload::kStaged, nullptr,
-                   &plan);
+  st = create_plan(im, workspace, workspace_bytes, static_cast<hipStream_t>(stream),
+                   Upload::kStaged, &plan);
   if (st != SIFT_OK) return st;
   st = sift_plan_run(plan, q, k, v, local_bitmap, cross_bitmap, softmax_scale, out, stream);
   const sift_status st2 = sift_plan_destroy(plan);  // host state only: the workspace is the caller's
@@ -1014,9 +1124,7 @@ sift_status sift_sparse_prefill_ex(const sift_tensor* q, const sift_tensor* k,
 
 sift_status sift_decode_workspace_bytes(const sift_layout* layout, int32_t num_q_heads,
                                         int32_t tile, size_t* bytes) {
-  if (bytes == nullptr) return SIFT_E_NULL;
-  return create_plan(layout, num_q_heads, kDecodeKvHeads, kDecodeHeadDim, tile, nullptr, 0,
-                     nullptr, Upload::kBlocking, bytes, nullptr);
+  return sift_workspace_bytes(layout, num_q_heads, kDecodeKvHeads, kDecodeHeadDim, tile, bytes);
 }
 
 sift_status sift_decode_tiles(const sift_layout* layout, const uint8_t* local_bitmap,
@@ -1026,22 +1134,20 @@ sift_status sift_decode_tiles(const sift_layout* layout, const uint8_t* local_bi
   if (layout == nullptr || row_ptr == nullptr || workspace == nullptr) return SIFT_E_NULL;
   if (num_q_heads < 1) return SIFT_E_SHAPE;
   if (tile != 16 && tile != 32 && tile != 64 && tile != 128) return SIFT_E_UNSUPPORTED;
-  HostPlan hp;
-  sift_status st = build_host_plan(layout, num_q_heads, kDecodeKvHeads, tile, hp);
+  PlanImage im;
+  sift_status st = make_image(layout, num_q_heads, kDecodeKvHeads, kDecodeHeadDim, tile, im);
   if (st != SIFT_OK) return st;
+  const HostPlan& hp = im.hp;
   if (hp.la_bytes > 0 && local_bitmap == nullptr) return SIFT_E_NULL;
   if (hp.ca_bytes > 0 && cross_bitmap == nullptr) return SIFT_E_NULL;
   const int64_t cap = hp.dense_tiles * num_q_heads;
   if (cap > 0 && col_idx == nullptr) return SIFT_E_NULL;
   if (col_capacity < cap) return SIFT_E_CAPACITY;
-  size_t need = 0;
-  if ((st = sift_decode_workspace_bytes(layout, num_q_heads, tile, &need)) != SIFT_OK) return st;
-  if (workspace_bytes < need) return SIFT_E_CAPACITY;
+  if (workspace_bytes < im.total) return SIFT_E_CAPACITY;
   if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return SIFT_E_UNSUPPORTED;
   sift_plan* plan = nullptr;
-  st = create_plan(layout, num_q_heads, kDecodeKvHeads, kDecodeHeadDim, tile, workspace,
-                   workspace_bytes, static_cast<hipStream_t>(stream), Upload::kStaged, nullptr,
-                   &plan);
+  st = create_plan(im, workspace, workspace_bytes, static_cast<hipStream_t>(stream),
+                   Upload::kStaged, &plan);
   if (st != SIFT_OK) return st;
   st = sift_plan_decode_tiles(plan, local_bitmap, cross_bitmap, row_ptr, col_idx, col_capacity,
                               stream);
@@ -1054,18 +1160,17 @@ sift_status sift_sparse_prefill_static(const sift_tensor* q, const sift_tensor* 
                                        const uint8_t* local_bitmap, const uint8_t* cross_bitmap,
                                        int32_t tile, float softmax_scale, sift_tensor* out,
                                        void* stream) {
-  size_t need = 0;
-  sift_status st = check_prefill(q, k, v, doc_offsets, local_bitmap, cross_bitmap, tile, out,
-                                 &need);
+  PlanImage im;
+  sift_status st = check_prefill(q, k, v, doc_offsets, local_bitmap, cross_bitmap, tile, out, im);
   if (st != SIFT_OK) return st;
-  if (need > kStaticScratchBytes) return SIFT_E_CAPACITY;
+  if (im.total > kStaticScratchBytes) return SIFT_E_CAPACITY;
   void* ws = nullptr;
   if ((st = static_scratch(&ws)) != SIFT_OK) return st;
   // tables from host memory: the call waits for the copy, so nothing is
   // allocated to hold them
   sift_plan* plan = nullptr;
-  st = create_plan(doc_offsets, q->heads, k->heads, q->head_dim, tile, ws, kStaticScratchBytes,
-                   static_cast<hipStream_t>(stream), Upload::kPageable, nullptr, &plan);
+  st = create_plan(im, ws, kStaticScratchBytes, static_cast<hipStream_t>(stream),
+                   Upload::kPageable, &plan);
   if (st != SIFT_OK) return st;
   st = sift_plan_run(plan, q, k, v, local_bitmap, cross_bitmap, softmax_scale, out, stream);
   const sift_status st2 = sift_plan_destroy(plan);  // host state only

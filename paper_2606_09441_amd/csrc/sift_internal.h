@@ -6,7 +6,14 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <functional>
+
 namespace sift {
+
+// n bytes to device memory in the order of `stream`, from pinned memory that
+// the library keeps and `fill` writes; returns without waiting (sift_api.cpp).
+hipError_t upload_staged(void* dst, size_t n, hipStream_t stream,
+                         const std::function<void(uint8_t*)>& fill);
 
 enum SegKind : int32_t { kDocument = 0, kQuery = 1 };
 
