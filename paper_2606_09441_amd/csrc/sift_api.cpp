@@ -119,6 +119,7 @@ struct HostPlan {
   int64_t head_steps = 0, head_work = 0;  // bound of the steps, and work units, of one head
   int64_t step_cap = 0;     // bound of all list units' steps
   int64_t chunk_size = 0;
+  bool scheduled = false;   // whether the decode has a schedule pass
   int64_t part_slots = 0;
   int64_t dense_tiles = 0;  // causal tiles of all prompts, one head
   int64_t la_bytes = 0, ca_bytes = 0;
@@ -614,7 +615,9 @@ sift_status make_image(const sift_layout* layout, int32_t num_q_heads, int32_t n
   im.tile_info = ints(hp.tile_info);
   im.urec = place(hp.num_urec * sizeof(sift::UnitRec));
   im.rec = place(hp.num_work * sizeof(sift::WorkRec));  // counts and first steps: by decode
-  im.launch = place(hp.chunk_size * sift::kNumXcd * sizeof(sift::WorkRec));  // by the schedule pass
+  hp.scheduled = hp.num_work > sift::kUnscheduled;
+  const int64_t slots = hp.scheduled ? hp.chunk_size * sift::kNumXcd : 0;
+  im.launch = place(slots * sizeof(sift::WorkRec));  // by the schedule pass
   im.splits = place(hp.num_splits * 4 * sizeof(int32_t));
   im.hist = place(kHistWords * sizeof(int32_t));
   im.upload = at;
@@ -668,8 +671,9 @@ void write_tables(const PlanImage& im, uint8_t* out) {
   // schedule pass fills those of the work units
   sift::WorkRec empty{};
   empty.slot = -1;
-  std::fill_n(reinterpret_cast<sift::WorkRec*>(out + im.launch), hp.chunk_size * sift::kNumXcd,
-              empty);
+  if (hp.scheduled)
+    std::fill_n(reinterpret_cast<sift::WorkRec*>(out + im.launch), hp.chunk_size * sift::kNumXcd,
+                empty);
   write_splits(hp, reinterpret_cast<int32_t*>(out + im.splits));
   std::memset(out + im.hist, 0, kHistWords * sizeof(int32_t));
 }
@@ -747,8 +751,8 @@ sift_status create_plan(const PlanImage& im, void* ws, size_t ws_bytes, hipStrea
   plan->pt.num_segments = hp.num_segments;
   plan->pt.num_q_heads = im.hq;
   plan->wt.rec = reinterpret_cast<sift::WorkRec*>(P(im.rec));
-  plan->wt.launch = reinterpret_cast<sift::WorkRec*>(P(im.launch));
-  plan->wt.hist = P(im.hist);
+  plan->wt.launch = hp.scheduled ? reinterpret_cast<sift::WorkRec*>(P(im.launch)) : plan->wt.rec;
+  plan->wt.hist = hp.scheduled ? P(im.hist) : nullptr;
   plan->wt.urec = reinterpret_cast<const sift::UnitRec*>(P(im.urec));
   plan->wt.steps = reinterpret_cast<int2*>(P(im.steps));
   plan->wt.kvb = im.tile < 64 ? reinterpret_cast<int4*>(P(im.kvb)) : nullptr;
@@ -772,7 +776,8 @@ sift_status create_plan(const PlanImage& im, void* ws, size_t ws_bytes, hipStrea
   plan->wt.chunk_size = static_cast<int32_t>(hp.chunk_size);
   plan->wt.sched_blocks = static_cast<int32_t>(
       std::min<int64_t>(8, std::max<int64_t>(1, ceil_div(hp.chunk_size, sift::kSchedPerBlock))));
-  plan->wt.grid = static_cast<int32_t>(hp.chunk_size * sift::kNumXcd);
+  plan->wt.grid =
+      static_cast<int32_t>(hp.scheduled ? hp.chunk_size * sift::kNumXcd : hp.num_work);
   plan->counts = P(im.counts);
   plan->row_ptr = P(im.rowptr);
   plan->col_idx = P(im.col);

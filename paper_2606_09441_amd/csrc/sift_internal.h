@@ -113,6 +113,10 @@ __device__ __forceinline__ int32_t sched_bucket(int32_t cnt) {
   return cnt >= kSchedBuckets - 1 ? 0 : kSchedBuckets - 1 - cnt;
 }
 
+// Plans of at most kUnscheduled work units, which all run at once, have no
+// schedule pass: workgroup w runs record w.
+constexpr int kUnscheduled = 512;  // 256 CUs x 2 resident attention workgroups
+
 struct alignas(64) WorkRec {
   int32_t head;      // query head
   int32_t kv_head;   // its K/V head
@@ -155,9 +159,10 @@ constexpr int32_t kUnitLastPart = 16;  // writes the work units' step counts
 
 struct WorkTables {
   WorkRec* rec;               // [W] locality order (device memory)
-  WorkRec* launch;            // [grid] launch order (device scratch, written by the schedule pass)
+  WorkRec* launch;            // [grid] launch order (device scratch, written by the schedule
+                              // pass; without one, rec)
   int32_t* hist;              // [kNumXcd * kSchedBuckets] bucket sizes (device scratch, zero
-                              // between decodes)
+                              // between decodes); nullptr: no schedule pass
   const UnitRec* urec;        // [num_urec] the list units, or their parts, in decode write order
   int2* steps;                // the list units' steps, one unit after another (device scratch)
   int4* kvb;                  // per step, T < 64 only: word q = the first K/V row
@@ -194,7 +199,7 @@ struct WorkTables {
   int32_t num_splits;         // NS
   int32_t chunk_size;         // work units per XCD chunk
   int32_t sched_blocks;       // schedule blocks per chunk
-  int32_t grid;               // kNumXcd * chunk_size
+  int32_t grid;               // kNumXcd * chunk_size (without a schedule pass, num_work)
 };
 
 // Step counts of a list unit's work units w0 .. w0 + nw - 1 (pieces of len
@@ -206,6 +211,7 @@ __device__ __forceinline__ void write_work_counts(const WorkTables& wt, int32_t 
     const int32_t rest = cnt - k * len;
     const int32_t c = rest < 0 ? 0 : (rest > len ? len : rest);
     wt.rec[w0 + k].step_cnt = c;
+    if (wt.hist == nullptr) continue;  // no schedule pass
     const int32_t x = (w0 + k) / wt.chunk_size;
     wt.rec[w0 + k].rank = atomicAdd(&wt.hist[x * kSchedBuckets + sched_bucket(c)], 1);
   }
