@@ -488,15 +488,19 @@ struct Emitter {
   // group's first key row and key count, per kernel block (G M-blocks) the
   // OR of the listed bits and whether the group is the block's diagonal, and
   // the sub-tile mask.
+  // rl: the tile's {first row on the packed axis, length}, for local < P.
   __device__ __forceinline__ void emit_grouped(unsigned listed, int32_t n, int32_t local, int32_t P,
-                                               int lane) {
+                                               int2 rl, int lane) {
     lists(listed, n);
-    steps_grouped(listed, n, local, P, lane);
+    steps_grouped(listed, n, local, P, rl, lane);
   }
 
   __device__ __forceinline__ void steps_grouped(unsigned listed, int32_t n, int32_t local,
-                                                int32_t P, int lane) {
+                                                int32_t P, int2 rl, int lane) {
     const int G = pt->group;
+    // length of the group's last tile, for the group's first lane (a group
+    // never leaves the 64 lanes)
+    const int tail = __shfl(rl.y, min(63, lane + max(0, min(G, P - local) - 1)), 64);
     unsigned gl[4];
     gl[0] = listed;
 #pragma unroll
@@ -511,7 +515,7 @@ struct Emitter {
     const unsigned long long mu = __ballot(emits);
     if (emits) {
       const int cnt = min(G, P - local);
-      const int len = (cnt - 1) * pt->tile + pt->tile_len[n + cnt - 1];
+      const int len = (cnt - 1) * pt->tile + tail;
       unsigned lst = 0u, sm = 0u;
       for (int k = 0; k < nb; ++k)
 #pragma unroll
@@ -524,22 +528,57 @@ struct Emitter {
 #pragma unroll
       for (int b = 0; b < kUnitBlocks; ++b)
         if (n == m0 + G * b) diag |= 1u << b;
-      const int32_t idx = ps + __popcll(mu & below);
-      const int32_t row0 = kv_row0(*pt, pages, n);
-      const int2 st = make_int2(static_cast<int>(sm), len | static_cast<int>(lst << kStepListedShift) |
-                                                      static_cast<int>(diag << kStepDiagShift));
-      steps[idx] = st;
-      note_first(idx, st);
-      // the group's tiles are adjacent in the packed K/V; a page pool places
-      // each on its own
-      int4 kb = make_int4(row0, row0, row0, row0);
-      if (pages.table != nullptr) {
-        const int T = pt->tile;
-        if (cnt > 1) kb.y = kv_row0(*pt, pages, n + 1) - T;
-        if (cnt > 2) kb.z = kv_row0(*pt, pages, n + 2) - 2 * T;
-        if (cnt > 3) kb.w = kv_row0(*pt, pages, n + 3) - 3 * T;
+      put_group(ps + __popcll(mu & below), n, cnt, rl.x,
+                make_int2(static_cast<int>(sm), len | static_cast<int>(lst << kStepListedShift) |
+                                                    static_cast<int>(diag << kStepDiagShift)));
+    }
+    ps += __popcll(mu);
+  }
+
+  // One step of a group of cnt adjacent tiles from n, first row row0 in the
+  // packed K/V; a page pool places each tile on its own.
+  __device__ __forceinline__ void put_group(int32_t idx, int32_t n, int cnt, int32_t row0, int2 st) {
+    steps[idx] = st;
+    note_first(idx, st);
+    int4 kb = make_int4(row0, row0, row0, row0);
+    if (pages.table != nullptr) {
+      const int T = pt->tile;
+      kb.x = kb.y = kb.z = kb.w = kv_row0(*pt, pages, n);
+      if (cnt > 1) kb.y = kv_row0(*pt, pages, n + 1) - T;
+      if (cnt > 2) kb.z = kv_row0(*pt, pages, n + 2) - 2 * T;
+      if (cnt > 3) kb.w = kv_row0(*pt, pages, n + 3) - 3 * T;
+    }
+    wt->kvb[idx] = kb;
+  }
+
+  // T < 64, a query unit: the lanes hold 64 consecutive tiles n of the
+  // prompt, `on` for those of the part, all listed by every M-block from n on.
+  // cnt: tiles of the group that starts at n (0: none does), first row row0,
+  // length of the last tile tail.
+  __device__ __forceinline__ void emit_query(bool on, int32_t n, int cnt, int32_t row0, int tail) {
+    const unsigned all = (1u << nb) - 1u;
+    lists(!on ? 0u : n < m0 ? all : (all & ~((1u << (n - m0)) - 1u)), n);
+    const int G = pt->group;
+    const bool emits = on && cnt > 0;
+    const unsigned long long mu = __ballot(emits);
+    if (emits) {
+      unsigned lst = 0u, sm = 0u;
+      for (int k = 0; k < nb; ++k) {
+        // M-block k lists the group's tiles up to its own
+        const int upto = min(cnt, m0 + k - n + 1);
+        if (upto > 0) {
+          lst |= 1u << (k / G);
+          sm |= ((1u << upto) - 1u) << (G * k);
+        }
       }
-      wt->kvb[idx] = kb;
+      unsigned diag = 0u;
+#pragma unroll
+      for (int b = 0; b < kUnitBlocks; ++b)
+        if (n == m0 + G * b) diag |= 1u << b;
+      const int len = (cnt - 1) * pt->tile + tail;
+      put_group(ps + __popcll(mu & below), n, cnt, row0,
+                make_int2(static_cast<int>(sm), len | static_cast<int>(lst << kStepListedShift) |
+                                                    static_cast<int>(diag << kStepDiagShift)));
     }
     ps += __popcll(mu);
   }
@@ -632,11 +671,27 @@ __global__ __launch_bounds__(256) void decode_write(PlanTables pt, WorkTables wt
       }
     }
   };
+  // T < 64, a document unit: the LA bytes of the rows, all issued together
+  // (under the rows' conditions they are a chain of up to eight loads a
+  // round), and the tiles; the first before the cross-list copy
+  unsigned lab[kNb];
+  int2 lrl = make_int2(0, 0);
+  auto load_own = [&](int c0) {
+    const int j = c0 + lane;
+#pragma unroll
+    for (int k = 0; k < kNb; ++k) {
+      const int r = i + k;
+      // every address valid: lav is the document's own LA vector
+      lab[k] = lav[k < nb && j < r ? (r * (r + 1) / 2 + j) >> 3 : 0];
+    }
+    lrl = rowlen[2 * (sd0 + min(j, ur.pages - 1))];
+  };
   if (copy) {
     ncross = wt.seg_cross[h * pt.num_segments + s];
     load_copy(0);
   }
   if constexpr (!kGrouped) load_walk(start);
+  else if (!query) load_own(0);
   Emitter<kNb, kHalves> e;
   e.col = col;
   e.steps = wt.steps;
@@ -676,7 +731,7 @@ __global__ __launch_bounds__(256) void decode_write(PlanTables pt, WorkTables wt
   }
   // a part of a query unit starts after the earlier segments' tiles, which
   // every M-block lists
-  const int32_t skip = kGrouped && query ? pt.seg_tile0[ur.part_d0] - lo : 0;
+  const int32_t skip = kGrouped && query ? ur.part_t0 - lo : 0;
   const bool first_part = (ur.flags & kUnitFirstPart) != 0;
 #pragma unroll
   for (int k = 0; k < kNb; ++k) {
@@ -726,16 +781,39 @@ __global__ __launch_bounds__(256) void decode_write(PlanTables pt, WorkTables wt
       load_walk(c0);
     }
   } else if (query) {
-    // the same, segment by segment so that tile groups stay within one call
-    // (this record's segments of the prompt)
-    for (int d = ur.part_d0; d < ur.part_d1; ++d) {
-      const int last = d < s ? pt.seg_pages[d] - 1 : mlast - pt.seg_tile0[s];
-      for (int c0 = 0; c0 <= last; c0 += 64) {
-        const int j = c0 + lane;
-        const int n = pt.seg_tile0[d] + j;
-        unsigned listed = 0u;
-        if (j <= last) listed = n < m0 ? all : (all & ~((1u << (n - m0)) - 1u));
-        e.emit_grouped(listed, n, j, last + 1, lane);
+    // this record's tiles, 64 to a round whatever their segments; a chunk of
+    // rounds loads its tiles' segments, then what follows from them, together
+    // (segment by segment, with each round's loads where they were used, a part
+    // of eight 32-tile documents was the pass: 28 us.  A call of 4,224 tokens,
+    // T = 16, 8/1 heads 91 us, now 73; 32/8 heads 121 / 103; T = 32 106 / 94)
+    constexpr int kRounds = 4;
+    const int G = pt.group;
+    for (int c0 = ur.part_t0; c0 < ur.part_t1; c0 += 64 * kRounds) {
+      int sg[kRounds], cnt[kRounds], tail[kRounds];
+      int2 rl[kRounds];
+#pragma unroll
+      for (int q = 0; q < kRounds; ++q) {
+        const int n = min(c0 + 64 * q + lane, mlast);
+        sg[q] = pt.tile_seg[n];
+        rl[q] = rowlen[2 * n];
+      }
+#pragma unroll
+      for (int q = 0; q < kRounds; ++q) {
+        const int n = min(c0 + 64 * q + lane, mlast);
+        const int first = pt.seg_tile0[sg[q]];
+        const int end = min(first + pt.seg_pages[sg[q]], mlast + 1);
+        cnt[q] = ((n - first) & (G - 1)) == 0 ? min(G, end - n) : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < kRounds; ++q) {
+        const int n = min(c0 + 64 * q + lane, mlast);
+        tail[q] = rowlen[2 * (n + max(cnt[q], 1) - 1)].y;
+      }
+#pragma unroll
+      for (int q = 0; q < kRounds; ++q) {
+        if (c0 + 64 * q >= ur.part_t1) break;
+        const int n = c0 + 64 * q + lane;
+        e.emit_query(n < ur.part_t1, n, cnt[q], rl[q].x, tail[q]);
       }
     }
   } else {
@@ -759,24 +837,25 @@ __global__ __launch_bounds__(256) void decode_write(PlanTables pt, WorkTables wt
         for (int c0 = 0; c0 < Pe; c0 += 64) {
           const int b = c0 + lane;
           const bool on = b < Pe && get_bit(cav, b);
-          e.emit_grouped(on ? all : 0u, pt.seg_tile0[d] + b, b, Pe, lane);
+          e.emit_grouped(on ? all : 0u, pt.seg_tile0[d] + b, b, Pe,
+                         rowlen[2 * (pt.seg_tile0[d] + min(b, Pe - 1))], lane);
         }
       }
     }
     // LA rows i .. i+nb-1 of the document's triangle, tiles j = 0 .. i+nb-1;
     // row r lists j < r when its bit is set, and its diagonal j == r
-    const int i = m0 - pt.seg_tile0[s];
-    const int P = pt.seg_pages[s];
-    const uint8_t* lav = la + pt.seg_la_off[s] + static_cast<int64_t>(h) * la_nbytes(P);
     for (int c0 = 0; c0 < i + nb; c0 += 64) {
       const int j = c0 + lane;
       unsigned listed = 0u;
 #pragma unroll
       for (int k = 0; k < kNb; ++k) {
         const int r = i + k;
-        if (k < nb && j <= r && (j == r || get_bit(lav, r * (r + 1) / 2 + j))) listed |= 1u << k;
+        const unsigned bit = (lab[k] >> (7 - ((r * (r + 1) / 2 + j) & 7))) & 1u;
+        if (k < nb && (j == r || (j < r && bit != 0u))) listed |= 1u << k;
       }
-      e.emit_grouped(listed, pt.seg_tile0[s] + j, j, P, lane);
+      const int2 rl = lrl;
+      if (c0 + 64 < i + nb) load_own(c0 + 64);
+      e.emit_grouped(listed, sd0 + j, j, ur.pages, rl, lane);
     }
   }
   const int32_t cnt = e.ps - e.base;
@@ -969,8 +1048,8 @@ __global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
     }
     return listed;
   };
+  const int2* rowlen = reinterpret_cast<const int2*>(pt.tile_info);  // {first row, length} at 2 n
   if constexpr (!kGrouped) {
-    const int2* rowlen = reinterpret_cast<const int2*>(pt.tile_info);  // {first row, length} at 2 n
     for (int n0 = lo; n0 <= mlast && sorted; n0 += 64) {
       const int n = n0 + lane;
       const int2 rl = rowlen[2 * min(n, mlast)];
@@ -979,12 +1058,13 @@ __global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
     }
   } else {
     // segment by segment: a step's group of tiles stays within one window
-    for (int d = ur.part_d0; d <= ur.seg && sorted; ++d) {
+    for (int d = pt.seg_first[ur.seg]; d <= ur.seg && sorted; ++d) {
       const int t0 = pt.seg_tile0[d], P = pt.seg_pages[d];
       const int last = d < ur.seg ? P - 1 : mlast - t0;
       for (int c0 = 0; c0 <= last && sorted; c0 += 64) {
+        const int2 rl = rowlen[2 * (t0 + min(c0 + lane, P - 1))];
         const unsigned listed = window(t0 + c0, min(t0 + c0 + 64, t0 + last + 1));
-        e.steps_grouped(listed, t0 + c0 + lane, c0 + lane, P, lane);
+        e.steps_grouped(listed, t0 + c0 + lane, c0 + lane, P, rl, lane);
       }
     }
   }

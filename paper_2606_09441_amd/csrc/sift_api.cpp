@@ -377,8 +377,8 @@ sift_status build_host_plan(const sift_layout* lay, int32_t hq, int32_t hkv, int
       r.nwork = static_cast<int32_t>(x.parts);
       r.plen = static_cast<int32_t>(x.len);
       r.flags = (x.query ? sift::kUnitQuery : 0) | ((hp.tile_len[m0] > 64 ? 3 : 1) << 1);
-      r.part_d0 = hp.seg_first[sg];
-      r.part_d1 = sg + 1;
+      r.part_t0 = r.lo;
+      r.part_t1 = m0 + x.nb;
       r.part_skip = 0;
       if (!(x.query && G > 1)) {
         r.flags |= sift::kUnitFirstPart | sift::kUnitLastPart;
@@ -390,7 +390,8 @@ sift_status build_host_plan(const sift_layout* lay, int32_t hq, int32_t hkv, int
           return d < sg ? hp.seg_pages[d] : mlast - hp.seg_tile0[sg] + 1;
         };
         int32_t skip = 0;
-        for (int32_t d0 = r.part_d0; d0 <= sg;) {
+        const int32_t first = hp.seg_first[sg];
+        for (int32_t d0 = first; d0 <= sg;) {
           int32_t d1 = d0;
           int64_t t = 0, n = 0;
           while (d1 <= sg && (d1 == d0 || t + tiles(d1) <= kPartTiles)) {
@@ -399,10 +400,10 @@ sift_status build_host_plan(const sift_layout* lay, int32_t hq, int32_t hkv, int
             ++d1;
           }
           sift::UnitRec p = r;
-          p.part_d0 = d0;
-          p.part_d1 = d1;
+          p.part_t0 = hp.seg_tile0[d0];
+          p.part_t1 = d1 <= sg ? hp.seg_tile0[d1] : mlast + 1;
           p.part_skip = skip;
-          if (d0 == r.part_d0) p.flags |= sift::kUnitFirstPart;
+          if (d0 == first) p.flags |= sift::kUnitFirstPart;
           if (d1 == sg + 1) p.flags |= sift::kUnitLastPart;
           parts.push_back({p, t, off, w0, x.cost});
           skip += static_cast<int32_t>(n);

@@ -149,7 +149,7 @@ struct alignas(64) UnitRec {
   int32_t work0, nwork, plen;  // its work units: nwork pieces of plen steps from work0
   int32_t flags;              // kUnitQuery | hrows << 1 (T = 128: kernel blocks of the
                               // M-block, 3 or 1) | kUnitFirstPart | kUnitLastPart
-  int32_t part_d0, part_d1;   // T < 64 query unit: the part's segments [d0, d1)
+  int32_t part_t0, part_t1;   // T < 64 query unit: the part's tiles [t0, t1)
   int32_t part_skip;          // steps of the unit before the part
 };
 static_assert(sizeof(UnitRec) == 64, "one record per 64 bytes");
