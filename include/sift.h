@@ -222,7 +222,7 @@ sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sif
  * out rows of m = softmax over the keys of the listed tiles (causal inside
  * the diagonal tile, length-masked in partial tiles) times V.
  *   q, k, v      device tensors; dtype both SIFT_BF16 (MFMA kernel: D =
- *                128, T = 16, 32, 64 or 128) or both SIFT_F32 (VALU kernel:
+ *                128, T = 16, 32, 64 or 128) or both SIFT_F32 (fp32 MFMA:
  *                D = 64 or 128, T = 16, 32 or 64)
  *   row_ptr, col_idx   device lists in the format sift_decode_tiles writes,
  *                col_capacity entries of col_idx readable.  Entries outside

@@ -31,6 +31,7 @@ namespace sift {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // off a 16-byte line
 
 constexpr int kRows = 16;    // query rows of a wavefront, keys of a block
 constexpr int kWaves = 4;    // wavefronts of a workgroup, 16-row blocks of a group
@@ -56,8 +57,9 @@ __device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c) {
 }
 
 __device__ __forceinline__ f32x4 load4(const float* p) {
-  return *reinterpret_cast<const f32x4*>(p);
+  return *reinterpret_cast<const f32x4u*>(p);
 }
+__device__ __forceinline__ void store4(float* p, f32x4 x) { *reinterpret_cast<f32x4u*>(p) = x; }
 
 // Over the four lanes of a query (l, l ^ 16, l ^ 32, l ^ 48).
 __device__ __forceinline__ float quad_max(float x) {
@@ -231,8 +233,8 @@ __global__ __launch_bounds__(256, 4) void attn_f32_kernel(PlanTables pt, AttnArg
     for (int c = 0; c < kVc; ++c)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        *reinterpret_cast<f32x4*>(dst + 64 * c + 4 * r) =
-            f32x4{o[4 * c][r], o[4 * c + 1][r], o[4 * c + 2][r], o[4 * c + 3][r]} * inv;
+        store4(dst + 64 * c + 4 * r,
+               f32x4{o[4 * c][r], o[4 * c + 1][r], o[4 * c + 2][r], o[4 * c + 3][r]} * inv);
     return;
   }
   // the wavefronts' partial sums, each relative to 2^m
@@ -266,7 +268,7 @@ __global__ __launch_bounds__(256, 4) void attn_f32_kernel(PlanTables pt, AttnArg
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) acc += load4(&part[w][r * kLds + d]) * wt[w];
-    *reinterpret_cast<f32x4*>(out + ((qtok + r) * a.hq + h) * D + d) = acc * inv;
+    store4(out + ((qtok + r) * a.hq + h) * D + d, acc * inv);
   }
 }
 
@@ -480,8 +482,8 @@ __global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkT
   for (int c = 0; c < kVc; ++c)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      *reinterpret_cast<f32x4*>(dst + 64 * c + 4 * r) =
-          f32x4{o[4 * c][r], o[4 * c + 1][r], o[4 * c + 2][r], o[4 * c + 3][r]} * inv;
+      store4(dst + 64 * c + 4 * r,
+             f32x4{o[4 * c][r], o[4 * c + 1][r], o[4 * c + 2][r], o[4 * c + 3][r]} * inv);
 }
 
 // Merge the pieces of the split units: with M the largest reference max of
@@ -522,7 +524,7 @@ __global__ __launch_bounds__(256) void combine_kernel(WorkTables wt, AttnArgs a)
   const float inv = wsum > 0.f ? 1.f / wsum : wsum;
   float* dst = static_cast<float*>(a.out) + (tok * a.hq + rp->head) * D + d0;
 #pragma unroll
-  for (int c = 0; c < D / 64; ++c) *reinterpret_cast<f32x4*>(dst + 64 * c) = acc[c] * inv;
+  for (int c = 0; c < D / 64; ++c) store4(dst + 64 * c, acc[c] * inv);
 }
 
 template <int T, int D>
@@ -532,7 +534,8 @@ hipError_t launch_t(const PlanTables& pt, const WorkTables* wt, const AttnArgs& 
   const int64_t groups = (static_cast<int64_t>(pt.num_tiles) + tiles - 1) / tiles;
   const int64_t units = groups * pt.num_q_heads;
   if (units == 0) return hipSuccess;
-  if (wt != nullptr && (units >= kFewGroups || a.row_ptr == nullptr)) {
+  // K and V rows are whole 16-byte chunks of the DMA only from a 16-byte line on
+  if (wt != nullptr && f32_steps_take(a) && (units >= kFewGroups || a.row_ptr == nullptr)) {
     hipLaunchKernelGGL((attn_f32_unit_kernel<T, D>), dim3(wt->grid), dim3(64 * kUnitWaves), 0,
                        stream, *wt, a);
     const hipError_t e = hipGetLastError();

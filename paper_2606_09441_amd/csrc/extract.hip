@@ -74,6 +74,8 @@ __device__ __forceinline__ int key_of(int a, int j, int hf) {
 }
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4u __attribute__((ext_vector_type(4), aligned(2)));  // off a 16-byte line
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) __bf16 lds_bf16;
 constexpr int kBufferWord3 = 0x00020000;  // gfx9-family raw buffer resource word 3
 
@@ -127,7 +129,8 @@ __device__ __forceinline__ void scores(const __bf16* lds, const bf16x8 (&qf)[D /
   }
 }
 
-template <int D, int T>
+// kDma: K starts on a 16-byte line and is staged by DMA; else through registers.
+template <int D, int T, bool kDma>
 __global__ __launch_bounds__(256, 4) void extract_kernel(ExtractArgs a, int cap) {
   constexpr int kKS = D / 16;
   constexpr int kSub = T < kKB ? kKB / T : 1;  // tiles of a key block
@@ -160,7 +163,7 @@ __global__ __launch_bounds__(256, 4) void extract_kernel(ExtractArgs a, int cap)
 #pragma unroll
     for (int k = 0; k < kKS; ++k) {
       u32x4 x = u32x4{0u, 0u, 0u, 0u};
-      if (p < L) x = *reinterpret_cast<const u32x4*>(src + 16 * k);
+      if (p < L) x = *reinterpret_cast<const u32x4u*>(src + 16 * k);
       qf[k] = __builtin_bit_cast(bf16x8, x);
     }
   }
@@ -179,6 +182,18 @@ __global__ __launch_bounds__(256, 4) void extract_kernel(ExtractArgs a, int cap)
   const int lds_dma = static_cast<int>(reinterpret_cast<size_t>((lds_bf16*)lds)) +
                       16 * wave * D * 2;
   auto dma = [&](int kb) {
+    if constexpr (!kDma) {
+      const char* src = reinterpret_cast<const char*>(kdoc) + static_cast<int64_t>(kb) * kKB * row_bytes;
+#pragma unroll
+      for (int it = 0; it < 16 / kDmaRows; ++it) {
+        const int row = 16 * wave + it * kDmaRows + drow;
+        const int off = (off0 ^ (((it * kDmaRows) & (kCpr - 1)) << 4)) + it * kDmaRows * row_bytes;
+        u32x4 x = u32x4{0u, 0u, 0u, 0u};
+        if (kb * kKB + row < L) x = *reinterpret_cast<const u32x4u*>(src + off);
+        *reinterpret_cast<lds_u32x4*>(static_cast<size_t>(lds_dma + it * 1024 + lane * 16)) = x;
+      }
+      return;
+    }
     const unsigned long long ad = reinterpret_cast<unsigned long long>(kdoc) +
                                   static_cast<unsigned long long>(kb) * kKB * row_bytes;
     i32x4 rs = i32x4{static_cast<int>(static_cast<unsigned>(ad)),
@@ -405,8 +420,12 @@ template <int D, int T>
 void launch_extract_dt(const ExtractArgs& a, int nblocks, int max_len, hipStream_t stream) {
   constexpr int kBlockBytes = (T < kKB ? kKB / T : 1) * kQB * 4;  // a key block's row maxima
   const int cap = std::min((max_len + kKB - 1) / kKB, kMaxBytes<D> / kBlockBytes);
-  hipLaunchKernelGGL((extract_kernel<D, T>), dim3(nblocks, a.hq), dim3(256), cap * kBlockBytes,
-                     stream, a, cap);
+  if (reinterpret_cast<uintptr_t>(a.k) % 16 == 0)
+    hipLaunchKernelGGL((extract_kernel<D, T, true>), dim3(nblocks, a.hq), dim3(256),
+                       cap * kBlockBytes, stream, a, cap);
+  else
+    hipLaunchKernelGGL((extract_kernel<D, T, false>), dim3(nblocks, a.hq), dim3(256),
+                       cap * kBlockBytes, stream, a, cap);
 }
 
 }  // namespace

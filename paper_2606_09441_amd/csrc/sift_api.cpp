@@ -1006,7 +1006,7 @@ sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sif
   // fp32 inputs: over the steps where they are the last decode's, for packed K and V
   // (its only form when it wrote its lists to the caller's buffers)
   const bool steps = plan->steps_decoded && !plan->steps_paged;
-  if (steps && !plan->lists_own) a.row_ptr = nullptr;
+  if (steps && !plan->lists_own && sift::f32_steps_take(a)) a.row_ptr = nullptr;
   const hipError_t e = q->dtype == SIFT_BF16
                            ? sift::launch_attn_bf16(plan->pt, work(plan), a, s)
                            : sift::launch_attn_f32(plan->pt, steps ? &plan->wt : nullptr, a, s);

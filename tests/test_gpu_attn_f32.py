@@ -94,3 +94,25 @@ def test_nan_reaches_only_rows_that_list_its_tile():
                 elif m > n:
                     assert np.isnan(got[b:b + c, h]).all(), (h, m)
         dw.close()
+
+
+@pytest.mark.parametrize("shape", [SMALL, UNITS], ids=["small", "units"])
+def test_storage_off_a_16_byte_line(shape):
+    import torch
+    prompts, hq, hkv = shape
+    wl = W.custom(prompts, tile=32, hq=hq, hkv=hkv, d=64, dtype="f32", seed=4)
+    dw = G.DevWorkload(wl)
+    ref = dw.run()
+
+    def skew(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        buf[1:] = t.flatten()
+        return buf[1:].view(t.shape)
+
+    q, k, v, out = (skew(t) for t in (dw.q, dw.k, dw.v, ref))
+    out.zero_()
+    dw.plan.run(q, k, v, dw.la, dw.ca, out=out)
+    torch.cuda.synchronize()
+    assert out.data_ptr() % 16 == 4
+    assert G.max_abs(out.cpu(), ref.cpu()) <= 2 * G.F32_TOL
+    dw.close()

@@ -40,3 +40,20 @@ def test_bits(alpha, beta, gamma, d, lens, tile):
     for g, w, ambiguous in zip(got, want[:2], want[2:]):
         assert g.shape == w.shape
         assert not np.any((g ^ w) & ~ambiguous)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_storage_off_a_16_byte_line(d):
+    import torch
+    from paper_2606_09441_amd import extract_bits
+    offs, q, k = _inputs([300, 65, 1], 2, 1, d, 3)
+
+    def skew(x):
+        buf = torch.empty(x.size + 1, dtype=torch.bfloat16, device="cuda")
+        buf[1:] = torch.from_numpy(x).flatten()
+        return buf[1:].view(x.shape)
+
+    got = extract_bits(skew(q), skew(k), offs, tile=32, alpha=0.002, beta=0.004, gamma=0.1)
+    want = _gpu_bits(offs, q, k, 32, 0.002, 0.004, 0.1)
+    for g, w in zip(got, want):
+        assert np.array_equal(g.cpu().numpy(), w)
