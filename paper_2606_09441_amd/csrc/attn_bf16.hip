@@ -596,8 +596,8 @@ __device__ __forceinline__ void combine_job(const WorkTables& wt, const AttnArgs
   }
 }
 
-// kRedo = false: the first pass; workgroup b takes the unit of launch slot
-// b and flags the launch (wt.redo[0]) if a weight check fails.  kRedo =
+// kRedo = false: the first pass; workgroup b takes its unit (launch_rec)
+// and flags the launch (wt.redo[0]) if a weight check fails.  kRedo =
 // true: the exact pass; when the flag is set, kRedoGrid workgroups do every
 // unit again, then the last one to finish clears the flag for the next
 // launch; otherwise they return at once.
@@ -614,7 +614,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(KernArgs ka) {
   __shared__ int slot_park;
 
   if constexpr (!kRedo) {
-    const int4* __restrict__ rp = reinterpret_cast<const int4*>(wt.launch + blockIdx.x);
+    const int4* __restrict__ rp = launch_rec(wt, blockIdx.x);
 #include "attn_bf16_unit.inc"
   } else {
     constexpr int kJobs = kUnitRows / 32;  // merge jobs per split unit

@@ -1142,9 +1142,8 @@ __global__ __launch_bounds__(1024) void schedule_scatter(WorkTables wt) {
 }
 
 hipError_t launch_schedule(const WorkTables& wt, hipStream_t stream) {
-  // few work units: all run at once, in any order, and the pass costs 5 us
-  // (us with / without: fp32, two documents of 128 tokens 26.5 / 20.5;
-  // 4,224 tokens, 8/1 heads 58 / 53, 14/2 heads, 490 units, 65 / 64)
+  // no pass (us with / without it, all work units running at once: fp32, two
+  // documents of 128 tokens 26.5 / 20.5; 4,224 tokens, 8/1 heads 58 / 53)
   if (wt.hist == nullptr) return hipSuccess;
   static_assert(kSchedBuckets == 1024, "one bucket per thread of the schedule pass");
   hipLaunchKernelGGL(schedule_scatter, dim3(kNumXcd * wt.sched_blocks), dim3(1024), 0, stream,

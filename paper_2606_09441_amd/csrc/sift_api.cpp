@@ -44,12 +44,30 @@ struct sift_plan {
   bool steps_paged = false;    // the last decode wrote page-pool rows into the steps
   bool steps_decoded = false;  // the steps are the last decode's (not merged caller lists)
   bool lists_own = false;      // the last decode wrote row_ptr and col_idx above
+  bool unsorted = false;       // bf16 calls leave the schedule pass out (kFewChunked)
   hipStream_t last_stream = nullptr;  // the stream of the plan's last enqueued work
 };
 
 namespace {
-// Everything an attention launch needs from the plan.
-sift::WorkTables work(const sift_plan* p) { return p->wt; }
+// The attention takes the records themselves, chunk by chunk, and there is no
+// schedule pass.
+void run_in_place(sift::WorkTables& wt) {
+  wt.launch = wt.rec;
+  wt.hist = nullptr;
+  wt.xcd_stride = wt.chunk_size;
+  wt.slot_stride = 1;
+}
+
+// Everything a decode or an attention launch needs from the plan.  sorted: the
+// call decodes and attends in one, over fp32 inputs.  The records are good after
+// any decode or merge, the launch slots only after one with a schedule pass,
+// so an attention that does not follow its own decode never reads those of an
+// unsorted plan.
+sift::WorkTables work(const sift_plan* p, bool sorted) {
+  sift::WorkTables wt = p->wt;
+  if (p->unsorted && !sorted) run_in_place(wt);
+  return wt;
+}
 }  // namespace
 
 namespace {
@@ -119,6 +137,7 @@ struct HostPlan {
   int64_t head_steps = 0, head_work = 0;  // bound of the steps, and work units, of one head
   int64_t step_cap = 0;     // bound of all list units' steps
   int64_t chunk_size = 0;
+  bool chunked = false;     // whether each chunk is whole kv heads
   bool scheduled = false;   // whether the decode has a schedule pass
   int64_t part_slots = 0;
   int64_t dense_tiles = 0;  // causal tiles of all prompts, one head
@@ -615,10 +634,11 @@ sift_status make_image(const sift_layout* layout, int32_t num_q_heads, int32_t n
   im.tile_lo = ints(hp.tile_lo);
   im.tile_info = ints(hp.tile_info);
   im.urec = place(hp.num_urec * sizeof(sift::UnitRec));
-  im.rec = place(hp.num_work * sizeof(sift::WorkRec));  // counts and first steps: by decode
-  hp.scheduled = hp.num_work > sift::kUnscheduled;
-  const int64_t slots = hp.scheduled ? hp.chunk_size * sift::kNumXcd : 0;
-  im.launch = place(slots * sizeof(sift::WorkRec));  // by the schedule pass
+  hp.chunked = num_kv_heads % sift::kNumXcd == 0;
+  hp.scheduled = hp.num_work > sift::kFewUnits;
+  const int64_t slots = hp.chunk_size * sift::kNumXcd;
+  im.rec = place(slots * sizeof(sift::WorkRec));  // counts and first steps: by decode
+  im.launch = place((hp.scheduled ? slots : 0) * sizeof(sift::WorkRec));  // by the schedule pass
   im.splits = place(hp.num_splits * 4 * sizeof(int32_t));
   im.hist = place(kHistWords * sizeof(int32_t));
   im.upload = at;
@@ -669,12 +689,15 @@ void write_tables(const PlanImage& im, uint8_t* out) {
   write_unit_records(hp, reinterpret_cast<sift::UnitRec*>(out + im.urec));
   write_work_records(hp, reinterpret_cast<sift::WorkRec*>(out + im.rec));
   // launch slots start empty (one M-block of no rows, no steps); the
-  // schedule pass fills those of the work units
+  // schedule pass fills those of the work units.  Without one the records
+  // are the launch slots, and those past the work units stay empty
   sift::WorkRec empty{};
   empty.slot = -1;
+  const int64_t slots = hp.chunk_size * sift::kNumXcd;
+  std::fill_n(reinterpret_cast<sift::WorkRec*>(out + im.rec) + hp.num_work, slots - hp.num_work,
+              empty);
   if (hp.scheduled)
-    std::fill_n(reinterpret_cast<sift::WorkRec*>(out + im.launch), hp.chunk_size * sift::kNumXcd,
-                empty);
+    std::fill_n(reinterpret_cast<sift::WorkRec*>(out + im.launch), slots, empty);
   write_splits(hp, reinterpret_cast<int32_t*>(out + im.splits));
   std::memset(out + im.hist, 0, kHistWords * sizeof(int32_t));
 }
@@ -777,8 +800,12 @@ sift_status create_plan(const PlanImage& im, void* ws, size_t ws_bytes, hipStrea
   plan->wt.chunk_size = static_cast<int32_t>(hp.chunk_size);
   plan->wt.sched_blocks = static_cast<int32_t>(
       std::min<int64_t>(8, std::max<int64_t>(1, ceil_div(hp.chunk_size, sift::kSchedPerBlock))));
-  plan->wt.grid =
-      static_cast<int32_t>(hp.scheduled ? hp.chunk_size * sift::kNumXcd : hp.num_work);
+  plan->wt.grid = static_cast<int32_t>(hp.chunk_size * sift::kNumXcd);
+  plan->wt.xcd_stride = 1;
+  plan->wt.slot_stride = sift::kNumXcd;
+  if (hp.chunked && !hp.scheduled) run_in_place(plan->wt);
+  plan->unsorted = im.hkv == sift::kNumXcd && hp.scheduled &&
+                   hp.num_work <= sift::kFewChunked && im.tile >= 64 && im.head_dim == 128;
   plan->counts = P(im.counts);
   plan->row_ptr = P(im.rowptr);
   plan->col_idx = P(im.col);
@@ -902,9 +929,9 @@ sift_status sift_plan_get_info(const sift_plan* plan, sift_plan_info* info) {
   return SIFT_OK;
 }
 
-sift_status sift_plan_decode_tiles(sift_plan* plan, const uint8_t* local_bitmap,
-                                   const uint8_t* cross_bitmap, int32_t* row_ptr,
-                                   int32_t* col_idx, int64_t col_capacity, void* stream) {
+static sift_status decode_lists(sift_plan* plan, const uint8_t* local_bitmap,
+                                const uint8_t* cross_bitmap, int32_t* row_ptr, int32_t* col_idx,
+                                int64_t col_capacity, bool sorted, void* stream) {
   if (plan == nullptr || row_ptr == nullptr) return SIFT_E_NULL;
   if (plan->info.la_bytes > 0 && local_bitmap == nullptr) return SIFT_E_NULL;
   if (plan->info.ca_bytes > 0 && cross_bitmap == nullptr) return SIFT_E_NULL;
@@ -912,8 +939,8 @@ sift_status sift_plan_decode_tiles(sift_plan* plan, const uint8_t* local_bitmap,
   if (col_capacity < plan->info.list_capacity) return SIFT_E_CAPACITY;
   sift_status st = check_device(plan);
   if (st != SIFT_OK) return st;
-  const hipError_t e = sift::launch_decode(plan->pt, work(plan), local_bitmap, cross_bitmap,
-                                           plan->counts, row_ptr, col_idx,
+  const hipError_t e = sift::launch_decode(plan->pt, work(plan, sorted), local_bitmap,
+                                           cross_bitmap, plan->counts, row_ptr, col_idx,
                                            sift::KvPages{nullptr, 0},
                                            static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return SIFT_E_HIP;
@@ -922,6 +949,13 @@ sift_status sift_plan_decode_tiles(sift_plan* plan, const uint8_t* local_bitmap,
   plan->lists_own = row_ptr == plan->row_ptr;
   plan->last_stream = static_cast<hipStream_t>(stream);
   return SIFT_OK;
+}
+
+sift_status sift_plan_decode_tiles(sift_plan* plan, const uint8_t* local_bitmap,
+                                   const uint8_t* cross_bitmap, int32_t* row_ptr,
+                                   int32_t* col_idx, int64_t col_capacity, void* stream) {
+  return decode_lists(plan, local_bitmap, cross_bitmap, row_ptr, col_idx, col_capacity, false,
+                      stream);
 }
 
 sift_status sift_plan_decode(sift_plan* plan, const uint8_t* local_bitmap,
@@ -964,10 +998,10 @@ sift_status sift_sparse_attention(sift_plan* plan, const sift_tensor* q, const s
   hipError_t e;
   if (bf16) {
     // the bf16 kernel walks merged per-unit step lists: build them from the lists
-    e = sift::launch_merge_steps(plan->pt, work(plan), row_ptr, col_idx, col_capacity, s);
+    e = sift::launch_merge_steps(plan->pt, work(plan, false), row_ptr, col_idx, col_capacity, s);
     plan->steps_decoded = false;
     if (e == hipSuccess) plan->steps_paged = false;
-    if (e == hipSuccess) e = sift::launch_attn_bf16(plan->pt, work(plan), a, s);
+    if (e == hipSuccess) e = sift::launch_attn_bf16(plan->pt, work(plan, false), a, s);
   } else {
     // the plan's steps stay the last decode's
     e = sift::launch_attn_f32(plan->pt, nullptr, a, s);
@@ -976,9 +1010,9 @@ sift_status sift_sparse_attention(sift_plan* plan, const sift_tensor* q, const s
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }
 
-sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
-                                const sift_tensor* v, float softmax_scale, sift_tensor* out,
-                                void* stream) {
+static sift_status attend(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
+                          const sift_tensor* v, float softmax_scale, sift_tensor* out, bool sorted,
+                          void* stream) {
   if (plan == nullptr) return SIFT_E_NULL;
   const sift_plan_info& in = plan->info;
   sift_status st = check_io(q, k, v, out, in.num_tokens, in.num_q_heads, in.num_kv_heads,
@@ -1007,11 +1041,18 @@ sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sif
   // (its only form when it wrote its lists to the caller's buffers)
   const bool steps = plan->steps_decoded && !plan->steps_paged;
   if (steps && !plan->lists_own && sift::f32_steps_take(a)) a.row_ptr = nullptr;
+  const sift::WorkTables wt = work(plan, sorted);
   const hipError_t e = q->dtype == SIFT_BF16
-                           ? sift::launch_attn_bf16(plan->pt, work(plan), a, s)
-                           : sift::launch_attn_f32(plan->pt, steps ? &plan->wt : nullptr, a, s);
+                           ? sift::launch_attn_bf16(plan->pt, wt, a, s)
+                           : sift::launch_attn_f32(plan->pt, steps ? &wt : nullptr, a, s);
   plan->last_stream = s;
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
+}
+
+sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
+                                const sift_tensor* v, float softmax_scale, sift_tensor* out,
+                                void* stream) {
+  return attend(plan, q, k, v, softmax_scale, out, false, stream);
 }
 
 sift_status sift_plan_run(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
@@ -1026,9 +1067,11 @@ sift_status sift_plan_run(sift_plan* plan, const sift_tensor* q, const sift_tens
   if (st != SIFT_OK) return st;
   if (in.la_bytes > 0 && local_bitmap == nullptr) return SIFT_E_NULL;
   if (in.ca_bytes > 0 && cross_bitmap == nullptr) return SIFT_E_NULL;
-  st = sift_plan_decode(plan, local_bitmap, cross_bitmap, stream);
+  const bool sorted = q->dtype == SIFT_F32;
+  st = decode_lists(plan, local_bitmap, cross_bitmap, plan->row_ptr, plan->col_idx,
+                    in.list_capacity, sorted, stream);
   if (st != SIFT_OK) return st;
-  return sift_plan_attention(plan, q, k, v, softmax_scale, out, stream);
+  return attend(plan, q, k, v, softmax_scale, out, sorted, stream);
 }
 
 
@@ -1060,8 +1103,9 @@ sift_status sift_plan_run_paged(sift_plan* plan, const sift_tensor* q, const sif
     softmax_scale = 1.0f / std::sqrt(static_cast<float>(in.head_dim));
   const sift::KvPages pages{page_table, num_pages};
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = sift::launch_decode(plan->pt, work(plan), local_bitmap, cross_bitmap,
-                                     plan->counts, plan->row_ptr, plan->col_idx, pages, s);
+  const sift::WorkTables wt = work(plan, q->dtype == SIFT_F32);
+  hipError_t e = sift::launch_decode(plan->pt, wt, local_bitmap, cross_bitmap, plan->counts,
+                                     plan->row_ptr, plan->col_idx, pages, s);
   plan->last_stream = s;
   if (e != hipSuccess) return SIFT_E_HIP;
   plan->steps_paged = true;
@@ -1082,8 +1126,8 @@ sift_status sift_plan_run_paged(sift_plan* plan, const sift_tensor* q, const sif
   a.scale_log2 = softmax_scale * 1.4426950408889634f;
   a.out_f32 = out->dtype == SIFT_F32 ? 1 : 0;
   a.pages = pages;
-  e = q->dtype == SIFT_BF16 ? sift::launch_attn_bf16(plan->pt, work(plan), a, s)
-                            : sift::launch_attn_f32(plan->pt, &plan->wt, a, s);
+  e = q->dtype == SIFT_BF16 ? sift::launch_attn_bf16(plan->pt, wt, a, s)
+                            : sift::launch_attn_f32(plan->pt, &wt, a, s);
   plan->last_stream = s;
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }

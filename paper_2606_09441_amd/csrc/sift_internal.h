@@ -113,9 +113,30 @@ __device__ __forceinline__ int32_t sched_bucket(int32_t cnt) {
   return cnt >= kSchedBuckets - 1 ? 0 : kSchedBuckets - 1 - cnt;
 }
 
-// Plans of at most kUnscheduled work units, which all run at once, have no
-// schedule pass: workgroup w runs record w.
-constexpr int kUnscheduled = 512;  // 256 CUs x 2 resident attention workgroups
+// Without a schedule pass the attention runs the records themselves.
+//
+// Up to kFewUnits work units all run at once, in any order, and the pass costs
+// 5 us of a call.  Where the chunks are whole kv heads (a multiple of kNumXcd of
+// them) each XCD takes its own chunk: 16/8 heads, 416 units, bf16 66 / 56 us
+// (workgroup w on record w / by chunks), fp32 of 512 units 447 / 270.  Else
+// one chunk may hold every piece of the longest groups (12/1 heads, 420 units,
+// 59 / 67), and workgroup w runs record w.
+//
+// Up to kFewChunked work units a bf16 call at T >= 64 with kNumXcd kv heads runs
+// each chunk, a kv head, in its locality order, which is by the units' longest
+// possible lists and near enough to the true order.  us with the pass /
+// without, 128-token query: 32/8 heads, 576 units 57 / 51, 1120 units 94 / 87;
+// with a density of its own from 0.05 to 0.5 for every (document, head): 640
+// units 62 / 55, 1152 units 106 / 106, 1824 units 184 / 185, but 48/8 heads, 1872
+// units 150 / 156, 32/8 heads, 4640 units 801 / 817.  The pass stays: with more
+// kv heads (a chunk's second one would start its longest units halfway: 64/16
+// heads, 1024 units 73 / 79); for fp32, whose steps take six times as long, so
+// that a long unit that starts late costs more (1248 units 605 / 661); at T <
+// 64, where the bounds count tiles, of which a step holds up to two or four,
+// alike for query pieces of full steps and document units (T = 16, 1664 units
+// 156 / 216).
+constexpr int kFewUnits = 512;  // 256 CUs x 2 resident attention workgroups
+constexpr int kFewChunked = 1536;
 
 struct alignas(64) WorkRec {
   int32_t head;      // query head
@@ -158,7 +179,8 @@ constexpr int32_t kUnitFirstPart = 8;  // writes the rows' row_ptr
 constexpr int32_t kUnitLastPart = 16;  // writes the work units' step counts
 
 struct WorkTables {
-  WorkRec* rec;               // [W] locality order (device memory)
+  WorkRec* rec;               // [W] locality order (device memory; without a schedule pass
+                              // [grid], empty records at the end)
   WorkRec* launch;            // [grid] launch order (device scratch, written by the schedule
                               // pass; without one, rec)
   int32_t* hist;              // [kNumXcd * kSchedBuckets] bucket sizes (device scratch, zero
@@ -199,8 +221,16 @@ struct WorkTables {
   int32_t num_splits;         // NS
   int32_t chunk_size;         // work units per XCD chunk
   int32_t sched_blocks;       // schedule blocks per chunk
-  int32_t grid;               // kNumXcd * chunk_size (without a schedule pass, num_work)
+  int32_t grid;               // kNumXcd * chunk_size
+  int32_t xcd_stride;         // workgroup x + kNumXcd k runs launch[x * xcd_stride + k *
+  int32_t slot_stride;        // slot_stride]: 1, kNumXcd, or without a schedule pass chunk_size, 1
 };
+
+// The record that workgroup b of an attention launch runs.
+__device__ __forceinline__ const int4* launch_rec(const WorkTables& wt, int32_t b) {
+  return reinterpret_cast<const int4*>(wt.launch + b % kNumXcd * wt.xcd_stride +
+                                       b / kNumXcd * wt.slot_stride);
+}
 
 // Step counts of a list unit's work units w0 .. w0 + nw - 1 (pieces of len
 // steps), from the length of its list, counted in their schedule buckets.
