@@ -596,12 +596,13 @@ __device__ __forceinline__ void combine_job(const WorkTables& wt, const AttnArgs
   }
 }
 
-// kRedo = false: the first pass; workgroup b takes its unit (launch_rec)
-// and flags the launch (wt.redo[0]) if a weight check fails.  kRedo =
-// true: the exact pass; when the flag is set, kRedoGrid workgroups do every
-// unit again, then the last one to finish clears the flag for the next
+// kRedo = false: the first pass; workgroup b takes the unit of launch slot
+// b (kChunks: chunk_place; an instance of its own, so that large calls keep
+// the plain index) and flags the launch (wt.redo[0]) if a weight check fails.
+// kRedo = true: the exact pass; when the flag is set, kRedoGrid workgroups do
+// every unit again, then the last one to finish clears the flag for the next
 // launch; otherwise they return at once.
-template <bool kOutF32, int kG, bool kRedo>
+template <bool kOutF32, int kG, bool kRedo, bool kChunks>
 __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(KernArgs ka) {
   const PlanTables& pt = ka.pt;
   const WorkTables& wt = ka.wt;
@@ -614,7 +615,8 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(KernArgs ka) {
   __shared__ int slot_park;
 
   if constexpr (!kRedo) {
-    const int4* __restrict__ rp = launch_rec(wt, blockIdx.x);
+    const int4* __restrict__ rp = reinterpret_cast<const int4*>(
+        wt.launch + (kChunks ? chunk_place(wt, blockIdx.x) : static_cast<int32_t>(blockIdx.x)));
 #include "attn_bf16_unit.inc"
   } else {
     constexpr int kJobs = kUnitRows / 32;  // merge jobs per split unit
@@ -666,11 +668,16 @@ hipError_t launch_attn_bf16(const PlanTables& pt, const WorkTables& wt, const At
     constexpr bool kF = decltype(out_f32)::value;
     constexpr int kGr = decltype(group)::value;
     const KernArgs ka{pt, wt, a};
-    hipLaunchKernelGGL((attn_bf16_kernel<kF, kGr, false>), dim3(wt.grid), dim3(256), 0, stream, ka);
+    if (wt.by_chunks)
+      hipLaunchKernelGGL((attn_bf16_kernel<kF, kGr, false, true>), dim3(wt.grid), dim3(256), 0,
+                         stream, ka);
+    else
+      hipLaunchKernelGGL((attn_bf16_kernel<kF, kGr, false, false>), dim3(wt.grid), dim3(256), 0,
+                         stream, ka);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attn_bf16_kernel<kF, kGr, true>), dim3(kRedoGrid), dim3(256), 0, stream,
-                       ka);
+    hipLaunchKernelGGL((attn_bf16_kernel<kF, kGr, true, false>), dim3(kRedoGrid), dim3(256), 0,
+                       stream, ka);
     return hipGetLastError();
   };
   using I1 = std::integral_constant<int, 1>;

@@ -324,7 +324,8 @@ __global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkT
   constexpr int kDma = 8 / kDmaRows;         // instructions of a wavefront's 8 rows
   __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * kBuf];
 
-  const int4* __restrict__ rp = launch_rec(wt, blockIdx.x);
+  const int4* __restrict__ rp = reinterpret_cast<const int4*>(
+      wt.launch + (wt.by_chunks ? chunk_place(wt, blockIdx.x) : static_cast<int32_t>(blockIdx.x)));
   const int4 ra = rp[0];  // head, kv head, rank, slot
   const int4 rb = rp[1];  // first token and length of the two blocks
   const int4 rc = rp[2];  // step offset, step count

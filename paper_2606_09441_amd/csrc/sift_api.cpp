@@ -54,8 +54,7 @@ namespace {
 void run_in_place(sift::WorkTables& wt) {
   wt.launch = wt.rec;
   wt.hist = nullptr;
-  wt.xcd_stride = wt.chunk_size;
-  wt.slot_stride = 1;
+  wt.by_chunks = 1;
 }
 
 // Everything a decode or an attention launch needs from the plan.  sorted: the
@@ -801,8 +800,6 @@ sift_status create_plan(const PlanImage& im, void* ws, size_t ws_bytes, hipStrea
   plan->wt.sched_blocks = static_cast<int32_t>(
       std::min<int64_t>(8, std::max<int64_t>(1, ceil_div(hp.chunk_size, sift::kSchedPerBlock))));
   plan->wt.grid = static_cast<int32_t>(hp.chunk_size * sift::kNumXcd);
-  plan->wt.xcd_stride = 1;
-  plan->wt.slot_stride = sift::kNumXcd;
   if (hp.chunked && !hp.scheduled) run_in_place(plan->wt);
   plan->unsorted = im.hkv == sift::kNumXcd && hp.scheduled &&
                    hp.num_work <= sift::kFewChunked && im.tile >= 64 && im.head_dim == 128;

@@ -222,14 +222,13 @@ struct WorkTables {
   int32_t chunk_size;         // work units per XCD chunk
   int32_t sched_blocks;       // schedule blocks per chunk
   int32_t grid;               // kNumXcd * chunk_size
-  int32_t xcd_stride;         // workgroup x + kNumXcd k runs launch[x * xcd_stride + k *
-  int32_t slot_stride;        // slot_stride]: 1, kNumXcd, or without a schedule pass chunk_size, 1
+  int32_t by_chunks;          // workgroup b runs the record of chunk b % kNumXcd at place
+                              // b / kNumXcd (no schedule pass), else launch[b]
 };
 
-// The record that workgroup b of an attention launch runs.
-__device__ __forceinline__ const int4* launch_rec(const WorkTables& wt, int32_t b) {
-  return reinterpret_cast<const int4*>(wt.launch + b % kNumXcd * wt.xcd_stride +
-                                       b / kNumXcd * wt.slot_stride);
+// The same as the place of its record in launch[].
+__device__ __forceinline__ int32_t chunk_place(const WorkTables& wt, int32_t b) {
+  return b % kNumXcd * wt.chunk_size + b / kNumXcd;
 }
 
 // Step counts of a list unit's work units w0 .. w0 + nw - 1 (pieces of len
