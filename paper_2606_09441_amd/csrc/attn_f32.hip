@@ -72,14 +72,20 @@ __device__ __forceinline__ float quad_sum(float x) {
 }
 
 // The running row max (log2 domain) moves to the new scores' max mx where
-// that is larger: O and l are rescaled.
+// that is larger: O, l and the sum `part` not yet added to l are rescaled.
+//
+// A tile's or step's weights are summed apart, then added to l once: added to l
+// one by one each sum is rounded at l's size, an error that grows with the list
+// (16,384 keys, all but one of equal weight: 5e-5 of l, this way 4e-6).
 template <int D>
-__device__ __forceinline__ void rescale(float mx, float& mref, float& lsum, f32x4 (&o)[D / 16]) {
+__device__ __forceinline__ void rescale(float mx, float& mref, float& lsum, float& part,
+                                        f32x4 (&o)[D / 16]) {
   if (!__builtin_amdgcn_ballot_w64(mx > mref)) return;
   const float mnew = fmaxf(mref, mx);
   const float alpha = mref == -INFINITY ? 0.f : exp2f(mref - mnew);  // O and l are 0 then
   mref = mnew;
   lsum *= alpha;
+  part *= alpha;
 #pragma unroll
   for (int d = 0; d < D / 16; ++d) o[d] *= alpha;
 }
@@ -178,6 +184,7 @@ __global__ __launch_bounds__(256, 4) void attn_f32_kernel(PlanTables pt, AttnArg
     const int64_t tok = kv_row0(pt, a.pages, n);
     const int klen = pt.tile_len[n];
     const bool diag = n == m;
+    float sum = 0.f;  // the tile's weights
     for (int kb = 0; kb < kBlocks; ++kb) {
       // keys after the length or, on the diagonal, after the last query
       if (kRows * kb >= klen || (diag && kb > bi)) break;
@@ -209,18 +216,19 @@ __global__ __launch_bounds__(256, 4) void attn_f32_kernel(PlanTables pt, AttnArg
         }
       }
       const float mx = quad_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))) * c2;
-      rescale<D>(mx, mref, lsum, o);
+      rescale<D>(mx, mref, lsum, sum, o);
       const float base = mref == -INFINITY ? 0.f : mref;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float p = exp2f(fmaf(s[r], c2, -base));
-        lsum += p;
+        sum += p;
 #pragma unroll
         for (int c = 0; c < kVc; ++c)
 #pragma unroll
           for (int d = 0; d < 4; ++d) o[4 * c + d] = mfma(vf[r][c][d], p, o[4 * c + d]);
       }
     }
+    lsum += sum;
   }
 
   lsum = quad_sum(lsum);
@@ -450,7 +458,8 @@ __global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkT
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[kb][r]);
-    rescale<D>(quad_max(mx) * c2, mref, lsum, o);
+    float sum = 0.f;  // the step's weights
+    rescale<D>(quad_max(mx) * c2, mref, lsum, sum, o);
     const float base = mref == -INFINITY ? 0.f : mref;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
@@ -458,7 +467,7 @@ __global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkT
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float p = exp2f(fmaf(s[kb][r], c2, -base));
-        lsum += p;
+        sum += p;
 #pragma unroll
         for (int c = 0; c < kVc; ++c) {
           const f32x4 vf = lds4((va ^ (r << 4)) + (kRows * kb + r) * kRowB + c * 256);
@@ -467,6 +476,7 @@ __global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkT
         }
       }
     }
+    lsum += sum;
   }
 
   lsum = quad_sum(lsum);

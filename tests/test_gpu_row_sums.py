@@ -42,3 +42,29 @@ def test_extraction(x):
     for step, want in ((-8, 1), (8, 0)):
         _, ca = extract_bits(q, k, [0, L], tile=T, alpha=0.5, beta=beta, gamma=(count + step) / cells)
         assert int(ca[0]) >> 6 & 1 == want, (x, step)
+
+
+@pytest.mark.parametrize("kernel", ["units", "lists"])
+def test_fp32_attention(kernel):
+    """Every tile marked, v zero but for key 0: row p is 1 / (1 + p w), whose
+    error is that of the row sum: (32 + 256) 2^-24, and 8 roundings of the
+    weights and the quotient."""
+    import torch
+    from paper_2606_09441_amd import Plan
+    xs = (0.75, 1.5, 2.5)
+    q, k = _qk(xs, torch.float32)
+    v = torch.zeros_like(k)
+    v[0] = 1
+    with Plan([0, L, L], [0, 2], len(xs), 1, 64, 64) as plan:
+        la, ca = (torch.full((plan.info[n],), 255, dtype=torch.uint8, device="cuda")
+                  for n in ("la_bytes", "ca_bytes"))
+        if kernel == "units":
+            out = plan.run(q, k, v, la, ca)
+        else:
+            out = plan.attention(q, k, v, *plan.decode(la, ca))
+        torch.cuda.synchronize()
+    w = np.exp(-np.asarray(xs))
+    want = 1 / (1 + np.arange(L)[:, None] * w)
+    err = np.abs(out.cpu().numpy().astype(np.float64) / want[:, :, None] - 1).max((0, 2))
+    print(f"{kernel}: relative error {err}", flush=True)
+    assert err.max() <= (32 + 256 + 8) * 2.0 ** -24
