@@ -211,7 +211,10 @@ sift_status sift_plan_decode(sift_plan* plan, const uint8_t* local_bitmap,
  * second step of sift_plan_run.  Tensors, scale and output as in
  * sift_sparse_attention.  SIFT_E_PLAN (bf16 inputs) when the last decode on
  * the plan was the one of sift_plan_run_paged: its step lists index a page
- * pool; decode again first.
+ * pool; decode again first.  SIFT_E_PLAN (fp32 inputs) when the plan holds no
+ * lists of the last decode: none yet, or sift_plan_decode_tiles, whose lists
+ * are the caller's, and since then bf16 sift_sparse_attention, which replaced
+ * its step lists; decode again, or pass the lists to sift_sparse_attention.
  */
 sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
                                 const sift_tensor* v, float softmax_scale, sift_tensor* out,

@@ -321,7 +321,10 @@ __device__ __forceinline__ void dma_b128(int m0, int voff, const i32x4& rs) {
 
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-template <int T, int D>
+// kDma: K and V start on a 16-byte line; else they are staged through registers
+// (4,224 tokens, 32/8 heads, D = 128: T = 64 437 us by DMA / 429, T = 16 415 /
+// 455; over the lists 1430 and 1246).
+template <int T, int D, bool kDma>
 __global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkTables wt,
                                                                           AttnArgs a) {
   constexpr int kG = kStepKeys / T;          // tiles of a step
@@ -329,7 +332,7 @@ __global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkT
   constexpr int kRowB = D * 4;               // bytes of a staged row
   constexpr int kBuf = kStepKeys * kRowB;    // bytes of a staged K or V step
   constexpr int kDmaRows = 1024 / kRowB;     // rows of one DMA instruction
-  constexpr int kDma = 8 / kDmaRows;         // instructions of a wavefront's 8 rows
+  constexpr int kDmas = 8 / kDmaRows;        // instructions of a wavefront's 8 rows
   __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * kBuf];
 
   const int4* __restrict__ rp = reinterpret_cast<const int4*>(
@@ -361,6 +364,18 @@ __global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkT
     const unsigned long long ad =
         reinterpret_cast<unsigned long long>(base) +
         static_cast<unsigned long long>(row0 * row_bytes + static_cast<int64_t>(kvh) * kRowB);
+    if constexpr (!kDma) {
+      const char* src = reinterpret_cast<const char*>(ad);
+#pragma unroll
+      for (int it = 0; it < kDmas; ++it) {
+        f32x4 x = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (8 * wave + it * kDmaRows + drow < len)
+          x = load4(reinterpret_cast<const float*>(src + (off0 ^ ((it * kDmaRows) << 4)) +
+                                                   it * kDmaRows * row_bytes));
+        *reinterpret_cast<lds_f32x4*>(static_cast<size_t>(to + it * 1024 + lane * 16)) = x;
+      }
+      return;
+    }
     i32x4 rs = i32x4{static_cast<int>(static_cast<unsigned>(ad)),
                      static_cast<int>((ad >> 32) & 0xffff), (len - 1) * row_bytes + kRowB,
                      kBufferWord3};
@@ -368,7 +383,7 @@ __global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkT
 #pragma unroll
     for (int j = 0; j < 4; ++j) rs[j] = __builtin_amdgcn_readfirstlane(rs[j]);
 #pragma unroll
-    for (int it = 0; it < kDma; ++it)
+    for (int it = 0; it < kDmas; ++it)
       dma_b128(to + it * 1024, (off0 ^ ((it * kDmaRows) << 4)) + it * kDmaRows * row_bytes, rs);
   };
   const int2* __restrict__ steps = wt.steps + rc.x;
@@ -545,10 +560,14 @@ hipError_t launch_t(const PlanTables& pt, const WorkTables* wt, const AttnArgs& 
   const int64_t groups = (static_cast<int64_t>(pt.num_tiles) + tiles - 1) / tiles;
   const int64_t units = groups * pt.num_q_heads;
   if (units == 0) return hipSuccess;
-  // K and V rows are whole 16-byte chunks of the DMA only from a 16-byte line on
-  if (wt != nullptr && f32_steps_take(a) && (units >= kFewGroups || a.row_ptr == nullptr)) {
-    hipLaunchKernelGGL((attn_f32_unit_kernel<T, D>), dim3(wt->grid), dim3(64 * kUnitWaves), 0,
-                       stream, *wt, a);
+  if (wt != nullptr && (units >= kFewGroups || a.row_ptr == nullptr)) {
+    // K and V rows are whole 16-byte chunks of the DMA only from a 16-byte line on
+    if ((reinterpret_cast<uintptr_t>(a.k) | reinterpret_cast<uintptr_t>(a.v)) % 16 == 0)
+      hipLaunchKernelGGL((attn_f32_unit_kernel<T, D, true>), dim3(wt->grid),
+                         dim3(64 * kUnitWaves), 0, stream, *wt, a);
+    else
+      hipLaunchKernelGGL((attn_f32_unit_kernel<T, D, false>), dim3(wt->grid),
+                         dim3(64 * kUnitWaves), 0, stream, *wt, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || wt->num_splits == 0) return e;
     hipLaunchKernelGGL((combine_kernel<D>), dim3(8 * wt->num_splits), dim3(256), 0, stream, *wt, a);

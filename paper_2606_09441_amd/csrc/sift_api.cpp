@@ -1016,6 +1016,11 @@ static sift_status attend(sift_plan* plan, const sift_tensor* q, const sift_tens
                             in.head_dim, in.tile);
   if (st != SIFT_OK) return st;
   if (plan->steps_paged && q->dtype == SIFT_BF16) return SIFT_E_PLAN;  // steps index a page pool
+  // fp32 inputs: over the steps where they are the last decode's, for packed K and V, or over
+  // the plan's lists; neither is left when that decode wrote its lists to the caller's buffers
+  // and attention over caller-given lists has replaced its steps (or there was no decode)
+  const bool steps = plan->steps_decoded && !plan->steps_paged;
+  if (q->dtype == SIFT_F32 && !steps && !plan->lists_own) return SIFT_E_PLAN;
   if ((st = check_device(plan)) != SIFT_OK) return st;
   if (!(softmax_scale > 0.f) || !std::isfinite(softmax_scale))
     softmax_scale = 1.0f / std::sqrt(static_cast<float>(in.head_dim));
@@ -1034,10 +1039,7 @@ static sift_status attend(sift_plan* plan, const sift_tensor* q, const sift_tens
   a.scale_log2 = softmax_scale * 1.4426950408889634f;
   a.out_f32 = out->dtype == SIFT_F32 ? 1 : 0;
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  // fp32 inputs: over the steps where they are the last decode's, for packed K and V
-  // (its only form when it wrote its lists to the caller's buffers)
-  const bool steps = plan->steps_decoded && !plan->steps_paged;
-  if (steps && !plan->lists_own && sift::f32_steps_take(a)) a.row_ptr = nullptr;
+  if (!plan->lists_own) a.row_ptr = nullptr;  // never those of an older decode
   const sift::WorkTables wt = work(plan, sorted);
   const hipError_t e = q->dtype == SIFT_BF16
                            ? sift::launch_attn_bf16(plan->pt, wt, a, s)

@@ -330,9 +330,6 @@ hipError_t launch_attn_bf16(const PlanTables& pt, const WorkTables& wt, const At
 // fp32 attention reads row_ptr/col_idx or, where wt is not nullptr, may read
 // its merged steps and work records instead: those of the same lists (and
 // does where row_ptr is nullptr).
-inline bool f32_steps_take(const AttnArgs& a) {  // K and V as the steps' kernel needs them
-  return (reinterpret_cast<uintptr_t>(a.k) | reinterpret_cast<uintptr_t>(a.v)) % 16 == 0;
-}
 hipError_t launch_attn_f32(const PlanTables& pt, const WorkTables* wt, const AttnArgs& a,
                            hipStream_t stream);
 

@@ -116,3 +116,72 @@ def test_storage_off_a_16_byte_line(shape):
     assert out.data_ptr() % 16 == 4
     assert G.max_abs(out.cpu(), ref.cpu()) <= 2 * G.F32_TOL
     dw.close()
+
+
+def _skewed(t):
+    """t on storage 4 bytes off a 16-byte line."""
+    import torch
+    buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+    buf[1:] = t.flatten()
+    return buf[1:].view(t.shape)
+
+
+@pytest.mark.parametrize("tile,d", [(16, 64), (32, 128), (64, 64), (64, 128)])
+@pytest.mark.parametrize("shape", [SMALL, UNITS, SPLIT], ids=["small", "units", "split"])
+def test_lists_in_caller_buffers_and_skewed_storage(shape, tile, d):
+    """A decode into the caller's buffers leaves the plan's own lists those of
+    an older decode, of other bits here: attention on the plan uses the new
+    ones, also where K or V is off a 16-byte line (or in a pool that is)."""
+    import torch
+    prompts, hq, hkv = shape
+    wl = W.custom(prompts, tile=tile, hq=hq, hkv=hkv, d=d, dtype="f32", seed=tile + d)
+    dw = G.DevWorkload(wl)
+    ref = _ref(wl)
+    dw.plan.run(dw.q, dw.k, dw.v, ~dw.la, ~dw.ca)
+    dw.plan.decode(dw.la, dw.ca)
+    k, v = _skewed(dw.k), _skewed(dw.v)
+    outs = [dw.plan.attention_internal(*x) for x in
+            ((dw.q, dw.k, dw.v), (dw.q, k, dw.v), (dw.q, dw.k, v), (_skewed(dw.q), k, v))]
+    packed = dw.plan.run(dw.q, k, v, dw.la, dw.ca)
+    kp, vp, table = G.page_pool(wl, dw.k, dw.v)
+    paged = dw.plan.run_paged(dw.q, _skewed(kp), _skewed(vp), table, dw.la, dw.ca)
+    torch.cuda.synchronize()
+    assert k.data_ptr() % 16 == 4
+    errs = [G.max_abs(o.cpu().numpy(), ref) for o in outs + [packed, paged]]
+    G.say(f"f32 T={tile} D={d}: max-abs " + " ".join(f"{e:.2e}" for e in errs))
+    assert max(errs) <= G.F32_TOL
+    # staged by DMA or through registers, the same sums
+    assert all(torch.equal(o, outs[0]) for o in outs[1:])
+    assert torch.equal(paged, packed)
+    dw.close()
+
+
+def test_no_lists_of_the_last_decode():
+    """No decode yet, or one into the caller's buffers whose steps a bf16 call
+    over lists has replaced: refused, until the next decode."""
+    import torch
+
+    from paper_2606_09441_amd import SiftError
+    prompts, hq, hkv = SMALL
+    wl = W.custom(prompts, tile=32, hq=hq, hkv=hkv, d=128, dtype="f32", seed=7)
+    dw = G.DevWorkload(wl)
+    out = torch.full_like(dw.q, 3.0)
+
+    def refused():
+        with pytest.raises(SiftError) as e:
+            dw.plan.attention_internal(dw.q, dw.k, dw.v, out=out)
+        assert e.value.status == 7
+        torch.cuda.synchronize()
+        assert bool((out == 3.0).all())
+
+    refused()
+    rp, ci = dw.plan.decode(dw.la, dw.ca)
+    dw.plan.attention(*(t.to(torch.bfloat16) for t in (dw.q, dw.k, dw.v)), rp, ci)
+    refused()
+    got = [dw.plan.attention(dw.q, dw.k, dw.v, rp, ci)]
+    dw.plan.decode_internal(dw.la, dw.ca)
+    dw.plan.attention(*(t.to(torch.bfloat16) for t in (dw.q, dw.k, dw.v)), rp, ci)
+    got.append(dw.plan.attention_internal(dw.q, dw.k, dw.v))
+    ref = _ref(wl)
+    assert all(G.max_abs(o.cpu().numpy(), ref) <= G.F32_TOL for o in got)
+    dw.close()
