@@ -215,6 +215,8 @@ sift_status sift_plan_decode(sift_plan* plan, const uint8_t* local_bitmap,
  * lists of the last decode: none yet, or sift_plan_decode_tiles, whose lists
  * are the caller's, and since then bf16 sift_sparse_attention, which replaced
  * its step lists; decode again, or pass the lists to sift_sparse_attention.
+ * SIFT_E_CAPACITY (fp32 inputs) after sift_plan_decode_tiles on a plan of 2^23
+ * work units or more: pass the lists to sift_sparse_attention.
  */
 sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
                                 const sift_tensor* v, float softmax_scale, sift_tensor* out,

@@ -303,7 +303,8 @@ typedef __attribute__((address_space(3))) float lds_float;
 typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
 constexpr int kStepKeys = 64;
-constexpr int kUnitWaves = 8;
+constexpr int kUnitWaves = kF32UnitThreads / 64;  // of 16 rows
+static_assert(kUnitWaves * kRows == kUnitRows, "a wavefront per 16 rows");
 constexpr int kBufferWord3 = 0x00020000;  // gfx9-family raw buffer resource word 3
 
 __device__ __forceinline__ f32x4 lds4(int addr) {
@@ -325,7 +326,7 @@ __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" :
 // (4,224 tokens, 32/8 heads, D = 128: T = 64 437 us by DMA / 429, T = 16 415 /
 // 455; over the lists 1430 and 1246).
 template <int T, int D, bool kDma>
-__global__ __launch_bounds__(64 * kUnitWaves, 4) void attn_f32_unit_kernel(WorkTables wt,
+__global__ __launch_bounds__(kF32UnitThreads, 4) void attn_f32_unit_kernel(WorkTables wt,
                                                                           AttnArgs a) {
   constexpr int kG = kStepKeys / T;          // tiles of a step
   constexpr int kC = D / 16, kVc = D / 64;
@@ -560,14 +561,14 @@ hipError_t launch_t(const PlanTables& pt, const WorkTables* wt, const AttnArgs& 
   const int64_t groups = (static_cast<int64_t>(pt.num_tiles) + tiles - 1) / tiles;
   const int64_t units = groups * pt.num_q_heads;
   if (units == 0) return hipSuccess;
-  if (wt != nullptr && (units >= kFewGroups || a.row_ptr == nullptr)) {
+  if (wt != nullptr && f32_units_fit(*wt) && (units >= kFewGroups || a.row_ptr == nullptr)) {
     // K and V rows are whole 16-byte chunks of the DMA only from a 16-byte line on
     if ((reinterpret_cast<uintptr_t>(a.k) | reinterpret_cast<uintptr_t>(a.v)) % 16 == 0)
       hipLaunchKernelGGL((attn_f32_unit_kernel<T, D, true>), dim3(wt->grid),
-                         dim3(64 * kUnitWaves), 0, stream, *wt, a);
+                         dim3(kF32UnitThreads), 0, stream, *wt, a);
     else
       hipLaunchKernelGGL((attn_f32_unit_kernel<T, D, false>), dim3(wt->grid),
-                         dim3(64 * kUnitWaves), 0, stream, *wt, a);
+                         dim3(kF32UnitThreads), 0, stream, *wt, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || wt->num_splits == 0) return e;
     hipLaunchKernelGGL((combine_kernel<D>), dim3(8 * wt->num_splits), dim3(256), 0, stream, *wt, a);

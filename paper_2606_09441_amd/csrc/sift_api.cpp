@@ -1020,7 +1020,10 @@ static sift_status attend(sift_plan* plan, const sift_tensor* q, const sift_tens
   // the plan's lists; neither is left when that decode wrote its lists to the caller's buffers
   // and attention over caller-given lists has replaced its steps (or there was no decode)
   const bool steps = plan->steps_decoded && !plan->steps_paged;
-  if (q->dtype == SIFT_F32 && !steps && !plan->lists_own) return SIFT_E_PLAN;
+  if (q->dtype == SIFT_F32 && !plan->lists_own) {
+    if (!steps) return SIFT_E_PLAN;
+    if (!sift::f32_units_fit(plan->wt)) return SIFT_E_CAPACITY;  // steps that no launch could hold
+  }
   if ((st = check_device(plan)) != SIFT_OK) return st;
   if (!(softmax_scale > 0.f) || !std::isfinite(softmax_scale))
     softmax_scale = 1.0f / std::sqrt(static_cast<float>(in.head_dim));

@@ -329,7 +329,11 @@ hipError_t launch_attn_bf16(const PlanTables& pt, const WorkTables& wt, const At
                             hipStream_t stream);
 // fp32 attention reads row_ptr/col_idx or, where wt is not nullptr, may read
 // its merged steps and work records instead: those of the same lists (and
-// does where row_ptr is nullptr).
+// does where row_ptr is nullptr; then f32_units_fit(*wt) holds).
+constexpr int kF32UnitThreads = 512;  // of the workgroup that runs a work unit
+inline bool f32_units_fit(const WorkTables& wt) {  // a grid holds fewer than 2^32 threads
+  return static_cast<int64_t>(wt.grid) * kF32UnitThreads < int64_t(1) << 32;
+}
 hipError_t launch_attn_f32(const PlanTables& pt, const WorkTables* wt, const AttnArgs& a,
                            hipStream_t stream);
 

@@ -185,3 +185,36 @@ def test_no_lists_of_the_last_decode():
     ref = _ref(wl)
     assert all(G.max_abs(o.cpu().numpy(), ref) <= G.F32_TOL for o in got)
     dw.close()
+
+
+@pytest.mark.parametrize("prompts", [(1 << 17) - 1, 1 << 17])
+def test_work_units_at_the_limit_of_a_launch(prompts):
+    """Prompts of one token and 64 heads: 2^23 - 64 work units, whose workgroups
+    of 512 threads a grid just holds, and 2^23, which the list kernel takes.
+    Each row's only key is its own, so it is its V row, but for the rounding of
+    the weight and of its reciprocal."""
+    import torch
+
+    from paper_2606_09441_amd import Plan, SiftError
+    hq = 64
+    so = np.arange(prompts + 1)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    q = torch.randn(prompts, hq, 64, generator=gen, device="cuda")
+    k, v = (torch.randn(prompts, 1, 64, generator=gen, device="cuda") for _ in range(2))
+    none = torch.zeros(1, dtype=torch.uint8, device="cuda")
+    with Plan(so, so, hq, 1, 64, 64) as plan:
+        assert plan.info["num_work_units"] == prompts * hq
+        out = plan.run(q, k, v, none, none)
+        err = float((out - v).abs().max())
+        out.zero_()
+        rp, ci = plan.decode(none, none)
+        if prompts * hq < 1 << 23:
+            plan.attention_internal(q, k, v, out=out)
+        else:
+            with pytest.raises(SiftError) as e:
+                plan.attention_internal(q, k, v, out=out)
+            assert e.value.status == 5
+            plan.attention(q, k, v, rp, ci, out=out)
+        err = max(err, float((out - v).abs().max()))
+    G.say(f"{prompts * hq} units: max-abs {err:.2e}")
+    assert err <= 8 * 2.0 ** -24 * float(v.abs().max())
