@@ -183,8 +183,9 @@ sift_status sift_plan_decode_tiles(sift_plan* plan, const uint8_t* local_bitmap,
  *                sift_decode_workspace_bytes(layout, num_q_heads, tile)
  *                bytes, owned by the caller: the decode's tables and scratch
  * The tables are copied into the workspace on `stream` from pinned host
- * memory the library keeps; the call returns once the work is enqueued,
- * without waiting for the stream.  The workspace must stay allocated until
+ * memory the library keeps (a buffer for every call whose copy is still
+ * queued); the call returns once the work is enqueued, without waiting for
+ * the stream.  The workspace must stay allocated until
  * that work is done; calls sharing a workspace must be ordered.
  * Errors: SIFT_E_NULL, SIFT_E_LAYOUT, SIFT_E_SHAPE, SIFT_E_UNSUPPORTED,
  *   SIFT_E_CAPACITY (col_capacity or workspace too small), SIFT_E_HIP; all

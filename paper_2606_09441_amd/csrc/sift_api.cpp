@@ -8,9 +8,9 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
-#include <deque>
 #include <functional>
 #include <limits>
+#include <list>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -482,9 +482,11 @@ namespace {
 // Pinned host staging for stream-ordered uploads of plan tables.  A buffer
 // is handed out to one call at a time; after the call has enqueued its copy
 // it records an event, and the buffer is reused once that event has
-// completed (the copy has read it).  Buffers live until the process ends; a
-// call that finds kMaxStaging of them busy on its device waits for one of
-// those that are large enough rather than allocate another.
+// completed (the copy has read it).  No call waits: one that finds every
+// buffer busy makes another, so there are at most as many as calls were queued
+// at once (the copies of a program's own unfinished work).  Those beyond
+// kKeptStaging per device go back when a plan is destroyed, which waits for
+// the device anyway to free its memory.
 struct StagingBuf {
   int device;
   void* host;
@@ -492,55 +494,60 @@ struct StagingBuf {
   hipEvent_t done;
   bool taken;
 };
-constexpr size_t kMaxStaging = 64;
+constexpr size_t kKeptStaging = 64;
 std::mutex g_staging_mu;
-std::deque<StagingBuf> g_staging;  // references stay valid
+std::list<StagingBuf> g_staging;  // addresses stay valid
 
 // A pinned buffer of at least n bytes on the current device, not in use.
 sift_status staging_acquire(size_t n, StagingBuf** out) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return SIFT_E_HIP;
-  StagingBuf* busy = nullptr;
   {
     std::lock_guard<std::mutex> lock(g_staging_mu);
-    size_t held = 0;
     for (StagingBuf& b : g_staging) {
-      held += b.device == dev ? 1 : 0;
       if (b.taken || b.device != dev || b.cap < n) continue;
       const hipError_t q = hipEventQuery(b.done);
-      if (q == hipErrorNotReady) {
-        if (busy == nullptr) busy = &b;
-        continue;
-      }
+      if (q == hipErrorNotReady) continue;
       if (q != hipSuccess) return SIFT_E_HIP;
       b.taken = true;
       *out = &b;
       return SIFT_OK;
     }
-    if (held >= kMaxStaging && busy != nullptr) {
-      busy->taken = true;
-    } else {
-      busy = nullptr;
-      size_t cap = 1 << 16;
-      while (cap < n) cap <<= 1;
-      StagingBuf b{dev, nullptr, cap, nullptr, true};
-      if (hipHostMalloc(&b.host, cap, hipHostMallocDefault) != hipSuccess) return SIFT_E_HIP;
-      if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
-        (void)hipHostFree(b.host);
-        return SIFT_E_HIP;
-      }
-      g_staging.push_back(b);
-      *out = &g_staging.back();
-      return SIFT_OK;
-    }
   }
-  if (hipEventSynchronize(busy->done) != hipSuccess) {
-    std::lock_guard<std::mutex> lock(g_staging_mu);
-    busy->taken = false;
+  size_t cap = 1 << 16;
+  while (cap < n) cap <<= 1;
+  std::list<StagingBuf> made{{dev, nullptr, cap, nullptr, true}};
+  StagingBuf& b = made.front();
+  if (hipHostMalloc(&b.host, cap, hipHostMallocDefault) != hipSuccess) return SIFT_E_HIP;
+  if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
+    (void)hipHostFree(b.host);
     return SIFT_E_HIP;
   }
-  *out = busy;
+  std::lock_guard<std::mutex> lock(g_staging_mu);
+  g_staging.splice(g_staging.end(), made);
+  *out = &b;
   return SIFT_OK;
+}
+
+// Give back the device's idle buffers beyond kKeptStaging.  Freeing pinned
+// memory may wait for the device.
+void staging_trim(int dev) {
+  std::list<StagingBuf> spare;
+  {
+    std::lock_guard<std::mutex> lock(g_staging_mu);
+    size_t held = 0;
+    for (const StagingBuf& b : g_staging) held += b.device == dev ? 1 : 0;
+    for (auto it = g_staging.begin(); it != g_staging.end() && held > kKeptStaging;) {
+      const auto b = it++;
+      if (b->device != dev || b->taken || hipEventQuery(b->done) != hipSuccess) continue;
+      spare.splice(spare.end(), g_staging, b);
+      --held;
+    }
+  }
+  for (StagingBuf& b : spare) {
+    (void)hipEventDestroy(b.done);
+    (void)hipHostFree(b.host);
+  }
 }
 
 // Hand a buffer back; with record, once the copies enqueued on the stream so
@@ -903,6 +910,7 @@ sift_status sift_plan_destroy(sift_plan* plan) {
     // the plan's last work may still read its memory
     if (hipStreamSynchronize(plan->last_stream) != hipSuccess) st = SIFT_E_HIP;
     if (hipFree(plan->dev) != hipSuccess) st = SIFT_E_HIP;
+    staging_trim(plan->device);
   }
   delete plan;
   return st;
