@@ -543,7 +543,9 @@ def _plain(*ts) -> bool:
     GPU, and nothing recorded or transformed (autograd, forward mode,
     tracing, tensor subclasses)."""
     torch = _torch()
-    if torch.jit.is_tracing() or torch.autograd.forward_ad._current_level >= 0:
+    # the dual level is no public name: where it is missing a level may be open
+    level = getattr(torch.autograd.forward_ad, "_current_level", 0)
+    if torch.jit.is_tracing() or level >= 0:
         return False
     grad = torch.is_grad_enabled()
     return all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda

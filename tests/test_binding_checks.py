@@ -85,3 +85,15 @@ def test_bitmap_bytes_follow_section_4_3():
     # documents of 128 tokens at T = 16: P = 8, LA ceil(72/16) = 5 bytes, CA 1 byte, per head
     assert L.bitmap_bytes([0, 128, 256, 288], [0, 3], 2, 16) == (2 * 2 * 5, 2 * 2 * 1)
     assert L.bitmap_bytes([0, 40], [0, 1], 4, 16) == (0, 0)        # a query alone
+
+
+def test_layer_ops_without_the_frameworks_dual_level(monkeypatch):
+    """The level of forward-mode derivatives is no public name of the
+    framework: without it the layer's operations stay with the framework."""
+    import torch
+
+    from paper_2606_09441_amd._lib import rms_norm, silu_mul
+    monkeypatch.delattr(torch.autograd.forward_ad, "_current_level")
+    x = torch.ones(2, 64, dtype=torch.bfloat16)
+    assert rms_norm(x, x[0], 1e-5) is None
+    assert silu_mul(x, x) is None
