@@ -977,10 +977,15 @@ __device__ int merge_serial(const PlanTables& pt, const WorkTables& wt,
 // prompt's tiles 64 at a time, as the decode does, and takes each M-block's
 // entries of the window from its list (64 loaded per M-block, those of the
 // window being consecutive and distinct where the list ascends strictly),
-// through a byte per tile in LDS to the tile's lane.  A list that does not
+// through a byte per tile in LDS to the tile's lane.  The next window starts at
+// the first entry left in any list.  A list that does not
 // ascend strictly is merged by one lane instead.
 // Bound by latency: one dependent load per window.  One thread per unit took
 // 301 us for 260 tiles x 32 heads (T = 64); this takes 18.
+// Stepping over windows without entries is for sparse lists: the diagonals
+// alone, T = 16, a call by one thread per unit / with every window walked /
+// this: 200 documents of 60 tokens, 32 heads 166 / 697 / 152 us, 66,048 tokens,
+// 48 heads 769 / 1247 / 765.
 template <int kNb, bool kGrouped, bool kHalves>
 __global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
                                                    const int32_t* __restrict__ row_ptr,
@@ -1019,9 +1024,11 @@ __global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
   e.hrows = static_cast<unsigned>((ur.flags >> 1) & 3);
   e.below = (1ull << lane) - 1ull;
   bool sorted = true;  // uniform
+  int32_t ahead = 0;   // uniform: the first entry of any list after the last window
   // bit k: M-block m0 + k lists tile n0 + lane; entries below n1 are consumed
   auto window = [&](int n0, int n1) {
     unsigned listed = 0u;
+    ahead = INT32_MAX;
 #pragma unroll
     for (int k = 0; k < kNb; ++k) {
       if (k >= nb) break;
@@ -1041,7 +1048,10 @@ __global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
         if (n >= n0 && n < n1 && n <= m0 + k) mk[n - n0] = 1;
         const int adv = __popcll(in);
         it[k] += adv;
-        if (adv < 64 || !sorted) break;
+        if (adv < 64 || !sorted) {
+          if (adv < 64) ahead = min(ahead, __builtin_amdgcn_readlane(n, adv));
+          break;
+        }
         before = __builtin_amdgcn_readlane(n, 63);
       }
       listed |= static_cast<unsigned>(mk[lane]) << k;
@@ -1050,22 +1060,27 @@ __global__ __launch_bounds__(256) void merge_steps(PlanTables pt, WorkTables wt,
   };
   const int2* rowlen = reinterpret_cast<const int2*>(pt.tile_info);  // {first row, length} at 2 n
   if constexpr (!kGrouped) {
-    for (int n0 = lo; n0 <= mlast && sorted; n0 += 64) {
+    for (int n0 = lo; n0 <= mlast && sorted; n0 = ahead) {
       const int n = n0 + lane;
       const int2 rl = rowlen[2 * min(n, mlast)];
       const unsigned listed = window(n0, min(n0 + 64, mlast + 1));
       e.steps_at(listed, n, rl.x, rl.y);
     }
   } else {
-    // segment by segment: a step's group of tiles stays within one window
-    for (int d = pt.seg_first[ur.seg]; d <= ur.seg && sorted; ++d) {
-      const int t0 = pt.seg_tile0[d], P = pt.seg_pages[d];
-      const int last = d < ur.seg ? P - 1 : mlast - t0;
-      for (int c0 = 0; c0 <= last && sorted; c0 += 64) {
-        const int2 rl = rowlen[2 * (t0 + min(c0 + lane, P - 1))];
-        const unsigned listed = window(t0 + c0, min(t0 + c0 + 64, t0 + last + 1));
-        e.steps_grouped(listed, t0 + c0 + lane, c0 + lane, P, rl, lane);
+    // a window lies in one segment, from a step's first tile on, so that a
+    // step's group of tiles stays within it
+    int d = pt.seg_first[ur.seg], t0 = lo, P = pt.seg_pages[d];
+    for (int n0 = lo; n0 <= mlast && sorted; n0 = ahead) {
+      if (n0 >= t0 + P) {
+        ++d;
+        if (n0 >= pt.seg_tile0[d] + pt.seg_pages[d]) d = pt.tile_seg[n0];
+        t0 = pt.seg_tile0[d];
+        P = pt.seg_pages[d];
       }
+      const int c0 = (n0 - t0) & ~(pt.group - 1);
+      const int2 rl = rowlen[2 * (t0 + min(c0 + lane, P - 1))];
+      const unsigned listed = window(t0 + c0, min(min(t0 + c0 + 64, t0 + P), mlast + 1));
+      e.steps_grouped(listed, t0 + c0 + lane, c0 + lane, P, rl, lane);
     }
   }
   // nothing but entries to skip may be left

@@ -68,3 +68,42 @@ def test_merge(tile):
             else:
                 assert np.max(np.abs(out[a:a + c, h] - want)) <= G.BF16_TOL
     dw.close()
+
+
+@pytest.mark.parametrize("tile", [16, 32, 64, 128])
+def test_sparse_lists(tile):
+    """Lists with gaps of whole windows and segments, which the merge steps
+    over: the diagonals alone, the prompt's first tile and the diagonal, and a
+    few tiles at a stride that meets every place of a window and of a step."""
+    import torch
+    T = tile
+    prompts = [[3 * T + 1] * 70 + [T], [200 * T, 5, 63 * T, 7 * T, 130 * T + 3, 2 * T + 9], [150 * T],
+               [T] * 66 + [40 * T]]
+    wl = W.custom(prompts, tile=T, hq=2, hkv=1, d=128, dtype="bf16", seed=T)
+    dw = G.DevWorkload(wl)
+    lay = G.oracle_layout(wl)
+    M = lay.num_tiles
+    first = np.zeros(M, np.int64)
+    at = 0
+    for p in prompts:
+        n = sum(-(-x // T) for x in p)
+        first[at:at + n] = at
+        at += n
+    rows = np.tile(np.arange(M), wl.hq)
+    for tiles in (lambda r, a, m: [m], lambda r, a, m: sorted({a, m}),
+                  lambda r, a, m: sorted({*range(m, a - 1, -(67 + r % 3)), m}),
+                  lambda r, a, m: [x for x in range(a, m + 1) if (x - a) % 97 < 2]):
+        lists = [np.asarray(tiles(r, first[m], m), np.int64) for r, m in enumerate(rows)]
+        rp = np.concatenate([[0], np.cumsum([len(x) for x in lists])])
+        ci = np.concatenate(lists)
+        got = _attend(dw, rp, ci)
+        # the same entries, merged by one lane
+        want = _attend(dw, *_rebuild(rp, ci, lambda r, x: np.concatenate([x, [-5, -5]])))
+        assert torch.equal(got, want)
+        # the fp32 list kernel, which merges nothing
+        f32 = dw.plan.attention(dw.q.float(), dw.k.float(), dw.v.float(),
+                                torch.from_numpy(rp.astype(np.int32)).cuda(),
+                                torch.from_numpy(ci.astype(np.int32)).cuda()) if T < 128 else None
+        if f32 is not None:
+            assert G.max_abs(got.float().cpu(), f32.cpu()) <= G.BF16_TOL
+    dw.close()
