@@ -44,12 +44,21 @@ enum Split : int {
 };
 
 // Calls of fewer 64-row groups (over all heads) than this split every block
-// and walk the lists; larger ones run the work units, where the steps allow.
+// and walk the lists; larger ones run the work units, where there are steps.
 // A work unit is two groups: below 512 the units leave CUs idle and the
-// longest unit (32 steps and more, some 120 us) sets the time.  Both sides
-// in us, lists / units (64-token query, D = 128, T = 64; the last row T = 16):
-//   36 groups  36 / 67     264 groups   98 / 120    520 groups  501 / 238
-//   528 groups 294 / 151   544 groups  209 / 124    544 groups  136 / 135
+// longest unit (32 steps and more, some 120 us) sets the time; at 512 the
+// lists' workgroups, one per block, fill the chip twice over.  The attention
+// alone in us, lists / units, D = 128, T = 64 (T = 16), of documents + query:
+//    64 groups (1 x 400 + 64)     20 / 47 (20 / 46)
+//   264        (8 x 256 + 64)     77 / 107 (76 / 163)
+//   388        (12 x 500 + 64)   208 / 240 (206 / 217), the closest of 20 layouts below 512
+//   448        (2 x 1500 + 500)  134 / 261 (130 / 353)
+//   488        (6 x 600 + 64)    136 / 177 (131 / 186)
+// and from 512 groups on, the lists splitting query rows alone:
+//   528        (8 x 256 + 64)    216 / 155 (192 / 186)
+//   592        (8 x 256 + 300)   259 / 301 (235 / 310), the units' one loss of 13 layouts
+//   736        (3 x 900 + 64)    312 / 208 (383 / 217)
+//  1312        (20 x 500 + 200) 2069 / 603 (1825 / 555)
 constexpr int kFewGroups = 512;
 
 __device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c) {
