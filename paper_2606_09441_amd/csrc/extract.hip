@@ -17,11 +17,13 @@
 //           wavefront), from the scores formed again, but only of blocks
 //           where some row maximum passes beta.
 //
-// Bound by VALU issue in pass 1: counters show MFMA, exponentials and other
-// vector instructions taking turns (an FMA, an exponential, an add and half a
-// max per score, 95 instructions and 33 exponentials beside the 16 MFMAs of a
-// block), so what counts is fewer of them and more wavefronts to fill waits:
-// one K block in LDS and 110 registers give four on a SIMD.  32 documents x
+// Bound by VALU issue in pass 1: an FMA, an exponential, an add and half a max
+// per score beside the 16 MFMAs of a block.  By the counters the matrix cores
+// are busy 44% of the SIMD cycles, a block takes 33 exponentials, 10.3 vector
+// instructions are issued per MFMA (pass 2 included), and wavefronts wait to
+// issue for 41% of their time: so what counts is fewer of them and more
+// wavefronts to fill waits: one K block in LDS and 110 registers give four on a
+// SIMD.  32 documents x
 // 2048 tokens x 48 heads (T = 64, D = 128): 2.17 ms with all scores formed
 // twice and two compares each in pass 2; with the row maxima 1.53 ms at three
 // wavefronts, 1.19 at four; exponentials interleaved by hand with the next
