@@ -218,6 +218,9 @@ sift_status sift_plan_decode(sift_plan* plan, const uint8_t* local_bitmap,
  * its step lists; decode again, or pass the lists to sift_sparse_attention.
  * SIFT_E_CAPACITY (fp32 inputs) after sift_plan_decode_tiles on a plan of 2^23
  * work units or more: pass the lists to sift_sparse_attention.
+ * bf16 inputs after bf16 sift_sparse_attention on the plan: over that call's
+ * lists, which have replaced the decode's step lists; decode again first for
+ * the decode's.
  */
 sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
                                 const sift_tensor* v, float softmax_scale, sift_tensor* out,
@@ -235,7 +238,7 @@ sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sif
  *                the M-block's prompt or after the M-block are skipped;
  *                lists must be ascending.  A row whose list is empty gets 0.
  *                (bf16 inputs: the lists are first merged into the plan's
- *                per-unit step scratch.)
+ *                per-unit step scratch, in place of the last decode's.)
  *   softmax_scale  <= 0 selects 1/sqrt(D)
  *   out          device tensor [tokens][Hq][D], SIFT_BF16 or SIFT_F32 for
  *                bf16 inputs, SIFT_F32 for fp32 inputs.

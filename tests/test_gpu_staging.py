@@ -2,6 +2,8 @@
 however many calls wait on the stream: each has its tables in a pinned buffer of
 its own until its copy has read them."""
 
+import time
+
 import numpy as np
 import pytest
 
@@ -50,9 +52,11 @@ def test_calls_behind_long_work_do_not_wait():
             torch.mm(a, a, out=b)
         behind = torch.cuda.Event()
         behind.record()
+        start = time.perf_counter()
         got = [one(i) for i in range(CALLS)]
-        waited = behind.query()
+        waited, took = behind.query(), time.perf_counter() - start
         torch.cuda.synchronize()
+        G.say(f"{CALLS} calls enqueued in {1e3 * took:.1f} ms")
         assert not waited
         for i, s in enumerate(segs):
             if i % 3 == 2:
