@@ -218,6 +218,10 @@ sift_status sift_plan_decode(sift_plan* plan, const uint8_t* local_bitmap,
  * its step lists; decode again, or pass the lists to sift_sparse_attention.
  * SIFT_E_CAPACITY (fp32 inputs) after sift_plan_decode_tiles on a plan of 2^23
  * work units or more: pass the lists to sift_sparse_attention.
+ * Captured into a graph without its decode, fp32 inputs run over the plan's
+ * lists, those of its last decode at replay; bf16 inputs, and fp32 inputs after
+ * sift_plan_decode_tiles, over its step lists at replay, which no
+ * sift_plan_run_paged and no bf16 sift_sparse_attention may have replaced.
  * bf16 inputs after bf16 sift_sparse_attention on the plan: over that call's
  * lists, which have replaced the decode's step lists; decode again first for
  * the decode's.

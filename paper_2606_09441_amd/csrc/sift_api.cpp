@@ -44,6 +44,7 @@ struct sift_plan {
   bool steps_paged = false;    // the last decode wrote page-pool rows into the steps
   bool steps_decoded = false;  // the steps are the last decode's (not merged caller lists)
   bool lists_own = false;      // the last decode wrote row_ptr and col_idx above
+  unsigned long long decode_capture = 0;  // the graph capture it was part of (0: none)
   bool unsorted = false;       // bf16 calls leave the schedule pass out (kFewChunked)
   hipStream_t last_stream = nullptr;  // the stream of the plan's last enqueued work
 };
@@ -84,6 +85,14 @@ sift_status check_device(const sift_plan* plan) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return SIFT_E_HIP;
   return dev == plan->device ? SIFT_OK : SIFT_E_PLAN;
+}
+
+// The graph capture that the stream takes part in, 0 if none.
+unsigned long long capture_of(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(s, &status, &id) != hipSuccess) return 0;
+  return status == hipStreamCaptureStatusActive ? id : 0;
 }
 
 // Shapes and dtypes of one call against the plan's sizes.
@@ -952,6 +961,7 @@ static sift_status decode_lists(sift_plan* plan, const uint8_t* local_bitmap,
   plan->steps_paged = false;
   plan->steps_decoded = true;
   plan->lists_own = row_ptr == plan->row_ptr;
+  plan->decode_capture = capture_of(static_cast<hipStream_t>(stream));
   plan->last_stream = static_cast<hipStream_t>(stream);
   return SIFT_OK;
 }
@@ -1052,9 +1062,17 @@ static sift_status attend(sift_plan* plan, const sift_tensor* q, const sift_tens
   const hipStream_t s = static_cast<hipStream_t>(stream);
   if (!plan->lists_own) a.row_ptr = nullptr;  // never those of an older decode
   const sift::WorkTables wt = work(plan, sorted);
-  const hipError_t e = q->dtype == SIFT_BF16
-                           ? sift::launch_attn_bf16(plan->pt, wt, a, s)
-                           : sift::launch_attn_f32(plan->pt, steps ? &wt : nullptr, a, s);
+  hipError_t e;
+  if (q->dtype == SIFT_BF16) {
+    e = sift::launch_attn_bf16(plan->pt, wt, a, s);
+  } else {
+    // a graph that does not hold the decode replays over whatever the plan holds
+    // then: its lists are a decode's, its steps may be page-pool rows or a bf16
+    // call's merged lists
+    const unsigned long long cap = capture_of(s);
+    const bool keep = cap != 0 && cap != plan->decode_capture && plan->lists_own;
+    e = sift::launch_attn_f32(plan->pt, steps && !keep ? &wt : nullptr, a, s);
+  }
   plan->last_stream = s;
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }

@@ -218,3 +218,52 @@ def test_work_units_at_the_limit_of_a_launch(prompts):
         err = max(err, float((out - v).abs().max()))
     G.say(f"{prompts * hq} units: max-abs {err:.2e}")
     assert err <= 8 * 2.0 ** -24 * float(v.abs().max())
+
+
+@pytest.mark.parametrize("shape", [SMALL, UNITS], ids=["small", "units"])
+def test_captured_attention(shape):
+    """fp32 attention in a graph, with and without the decode in it: replays
+    after bf16 calls over other lists, which replace the plan's steps, give the
+    eager result."""
+    import torch
+    prompts, hq, hkv = shape
+    wl = W.custom(prompts, tile=64, hq=hq, hkv=hkv, d=128, dtype="f32", seed=11)
+    dw = G.DevWorkload(wl)
+    p, io = dw.plan, (dw.q, dw.k, dw.v)
+    half = tuple(t.to(torch.bfloat16) for t in io)
+    rows = p.info["num_rows"]
+    rp = torch.arange(rows + 1, dtype=torch.int32, device="cuda")
+    ci = torch.arange(p.info["num_tiles"], dtype=torch.int32, device="cuda").repeat(hq)
+    p.attention(*half, rp, ci)
+    want = dw.run()
+    assert G.max_abs(want.cpu(), _ref(wl)) <= G.F32_TOL
+    outs = [torch.empty_like(dw.q) for _ in range(3)]
+
+    def alone():
+        p.attention_internal(*io, out=outs[0])
+
+    def decode_first():
+        p.decode_internal(dw.la, dw.ca)
+        p.attention_internal(*io, out=outs[1])
+
+    def run():
+        p.run(*io, dw.la, dw.ca, out=outs[2])
+
+    for fn, out in zip((alone, decode_first, run), outs):
+        p.decode_internal(dw.la, dw.ca)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            fn()
+        for _ in range(3):
+            out.zero_()
+            p.attention(*half, rp, ci)     # other lists
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert G.max_abs(out.cpu(), want.cpu()) <= 2 * G.F32_TOL, fn.__name__
+            p.decode_internal(dw.la, dw.ca)
+            g.replay()
+            torch.cuda.synchronize()
+            assert G.max_abs(out.cpu(), want.cpu()) <= 2 * G.F32_TOL, fn.__name__
+    dw.close()
