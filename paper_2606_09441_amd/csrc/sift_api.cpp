@@ -44,7 +44,8 @@ struct sift_plan {
   bool steps_paged = false;    // the last decode wrote page-pool rows into the steps
   bool steps_decoded = false;  // the steps are the last decode's (not merged caller lists)
   bool lists_own = false;      // the last decode wrote row_ptr and col_idx above
-  unsigned long long decode_capture = 0;  // the graph capture it was part of (0: none)
+  unsigned long long decode_capture = 0;  // the graph capture it was part of (0: none, or
+                                          // sift_plan_run's, whose attention follows it)
   bool unsorted = false;       // bf16 calls leave the schedule pass out (kFewChunked)
   hipStream_t last_stream = nullptr;  // the stream of the plan's last enqueued work
 };
@@ -961,7 +962,7 @@ static sift_status decode_lists(sift_plan* plan, const uint8_t* local_bitmap,
   plan->steps_paged = false;
   plan->steps_decoded = true;
   plan->lists_own = row_ptr == plan->row_ptr;
-  plan->decode_capture = capture_of(static_cast<hipStream_t>(stream));
+  plan->decode_capture = 0;
   plan->last_stream = static_cast<hipStream_t>(stream);
   return SIFT_OK;
 }
@@ -969,8 +970,10 @@ static sift_status decode_lists(sift_plan* plan, const uint8_t* local_bitmap,
 sift_status sift_plan_decode_tiles(sift_plan* plan, const uint8_t* local_bitmap,
                                    const uint8_t* cross_bitmap, int32_t* row_ptr,
                                    int32_t* col_idx, int64_t col_capacity, void* stream) {
-  return decode_lists(plan, local_bitmap, cross_bitmap, row_ptr, col_idx, col_capacity, false,
-                      stream);
+  const sift_status st =
+      decode_lists(plan, local_bitmap, cross_bitmap, row_ptr, col_idx, col_capacity, false, stream);
+  if (st == SIFT_OK) plan->decode_capture = capture_of(static_cast<hipStream_t>(stream));
+  return st;
 }
 
 sift_status sift_plan_decode(sift_plan* plan, const uint8_t* local_bitmap,
@@ -1025,9 +1028,10 @@ sift_status sift_sparse_attention(sift_plan* plan, const sift_tensor* q, const s
   return e == hipSuccess ? SIFT_OK : SIFT_E_HIP;
 }
 
+// after_decode: the call's own decode precedes.
 static sift_status attend(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
-                          const sift_tensor* v, float softmax_scale, sift_tensor* out, bool sorted,
-                          void* stream) {
+                          const sift_tensor* v, float softmax_scale, sift_tensor* out,
+                          bool after_decode, bool sorted, void* stream) {
   if (plan == nullptr) return SIFT_E_NULL;
   const sift_plan_info& in = plan->info;
   sift_status st = check_io(q, k, v, out, in.num_tokens, in.num_q_heads, in.num_kv_heads,
@@ -1069,7 +1073,7 @@ static sift_status attend(sift_plan* plan, const sift_tensor* q, const sift_tens
     // a graph that does not hold the decode replays over whatever the plan holds
     // then: its lists are a decode's, its steps may be page-pool rows or a bf16
     // call's merged lists
-    const unsigned long long cap = capture_of(s);
+    const unsigned long long cap = after_decode ? 0 : capture_of(s);
     const bool keep = cap != 0 && cap != plan->decode_capture && plan->lists_own;
     e = sift::launch_attn_f32(plan->pt, steps && !keep ? &wt : nullptr, a, s);
   }
@@ -1080,7 +1084,7 @@ static sift_status attend(sift_plan* plan, const sift_tensor* q, const sift_tens
 sift_status sift_plan_attention(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
                                 const sift_tensor* v, float softmax_scale, sift_tensor* out,
                                 void* stream) {
-  return attend(plan, q, k, v, softmax_scale, out, false, stream);
+  return attend(plan, q, k, v, softmax_scale, out, false, false, stream);
 }
 
 sift_status sift_plan_run(sift_plan* plan, const sift_tensor* q, const sift_tensor* k,
@@ -1099,7 +1103,7 @@ sift_status sift_plan_run(sift_plan* plan, const sift_tensor* q, const sift_tens
   st = decode_lists(plan, local_bitmap, cross_bitmap, plan->row_ptr, plan->col_idx,
                     in.list_capacity, sorted, stream);
   if (st != SIFT_OK) return st;
-  return attend(plan, q, k, v, softmax_scale, out, sorted, stream);
+  return attend(plan, q, k, v, softmax_scale, out, true, sorted, stream);
 }
 
 
